@@ -535,8 +535,14 @@ __device__ __forceinline__ double ord_value(unsigned long long k, int nbits) {
     }
     return __longlong_as_double((long long)((k >> 63) ? (k & ~(1ull << 63)) : ~k));
 }
+// Below kMassCut the mass is zero whatever the rounding (e^kMassCut 2^40 < 0.98;
+// NaN and -inf differences too), and the exponential is not evaluated: most
+// samples of a peaked weight set.
+constexpr double kMassCut = -27.75;
 __device__ __forceinline__ unsigned long long mass_fx(double v, double vmax) {
-    return (unsigned long long)floor(exp(v - vmax) * (double)(1ull << kAvMassBits));
+    const double d = v - vmax;
+    if (!(d > kMassCut)) return 0ull;
+    return (unsigned long long)floor(exp(d) * (double)(1ull << kAvMassBits));
 }
 
 // Fair draws from weighted samples (k_fair.hip): scratch of

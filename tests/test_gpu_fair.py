@@ -55,6 +55,32 @@ def test_fair_draw_matches_oracle(orc, policy, n):
     assert np.array_equal(out.cpu().numpy(), th[:, o])
 
 
+@pytest.mark.parametrize("n,spread,shift", [
+    (63, 1.0, 0), (64, 1.0, 1), (65, 0.0, 0),           # one granule of 64 samples and its edges
+    (4096, 2.0, 1), (4097, 2.0, 3),                     # one tile, and a second one of one sample
+    (2048 * 4096 + 1, 9.0, 1),                          # more tiles than runs: two tiles per run
+])
+def test_fair_draw_granules_tiles_runs(orc, n, spread, shift):
+    """Indices equal to the oracle's at the edges of the granules, tiles and
+    runs that the masses are summed by, from a buffer that starts `shift`
+    values past an aligned address, with infinities of both signs."""
+    rng = np.random.default_rng(113 + n)
+    lw = rng.normal(0, spread, n).astype(np.float32)
+    lw[rng.choice(n, 2, replace=False)] = [np.inf, -np.inf]
+    job = _job(ile.ILE_FP32, seed=114)
+    k = 5003
+    try:
+        buf = torch.zeros(n + shift, dtype=torch.float32, device="cuda")
+        buf[shift:] = torch.from_numpy(lw).to("cuda")
+        idx = torch.full((k,), -7, dtype=torch.int64, device="cuda")
+        ile.ile_fair_draw(job, n, buf.data_ptr() + 4 * shift, 0xFA2, 5, k, idx)
+        torch.cuda.synchronize()
+    finally:
+        ile.ile_job_release(job)
+    lw = np.where(np.isfinite(lw), lw, -np.inf).astype(np.float64)
+    assert np.array_equal(idx.cpu().numpy(), orc.fair_draw(lw, 0xFA2, 5, k))
+
+
 def test_fair_draw_without_weight_and_errors():
     job = _job(ile.ILE_FP64, seed=112)
     try:
