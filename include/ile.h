@@ -413,12 +413,15 @@ ile_status ile_ac_get(ile_job *job, int32_t *n_dim, int32_t *dims, double *pi, i
  *     2, 4, 8, 16 dividing n that put the window on at most 64 decimated
  *     times (one 32- or 64-row tile of the product), by estimated cost;
  *     ILE_E_INVALID when there is none;
- *   ILE_QV_AUTO: the decimated route when it applies and its estimated cost
- *     is lower, else the direct one; also the direct one when the decimated
- *     route's scratch (16 B per grid bin and column, against 16 B per band
- *     bin and column) cannot be allocated within the context's budget.
- * The band lists are staged in pinned memory, so the call does not wait on
- * the stream before its final synchronisation. */
+ *   ILE_QV_AUTO: n / 512 interleaved FFTs of 512 points per block of 512
+ *     window times, summed with the phases e^{2 pi i m1 i / n} of the
+ *     interleave, when 512 divides n and the estimated cost is below the
+ *     direct sum's; else the decimated route when it applies and its
+ *     estimated cost is lower; else the direct one.  A route whose scratch
+ *     cannot be allocated within the context's budget gives way to the next
+ *     (the FFT needs 16 B per grid bin and detector, the decimated route 16 B
+ *     per grid bin and column, the direct one 16 B per band bin and column).
+ * The call does not wait on the stream before its final synchronisation. */
 #define ILE_QV_AUTO 0
 #define ILE_QV_DIRECT 1
 #define ILE_QV_DECIMATED 2

@@ -155,17 +155,25 @@ extern "C" ile_status ile_overlaps(ile_ctx *ctx, const ile_qv_shape *sh, const v
     if (!hlm || !data || !Q || !U || !V) return set_err(ILE_E_INVALID, "null array");
     if (sh->route < ILE_QV_AUTO || sh->route > ILE_QV_DECIMATED) return set_err(ILE_E_INVALID, "bad overlap route");
     const int64_t n = sh->n_freq;
-    std::vector<int64_t> band, msig;
-    for (int64_t m = 0; m < n; m++) {
-        const int64_t ms = m < (n + 1) / 2 ? m : m - n;   // FFT-order signed index
-        const double af = std::fabs((double)ms * sh->df);
-        if (af >= sh->f_lo && af <= sh->f_hi) {
-            band.push_back(m);
-            msig.push_back(ms);
-        }
+    // the band: bins m_lo .. m_hi of 0 <= m <= n / 2 and their mirrors n - m
+    // (|m' df| in [f_lo, f_hi], m' the signed index: the same test for both
+    // signs, and increasing in |m'|)
+    auto on = [&](int64_t m) {
+        const double af = std::fabs((double)m * sh->df);
+        return af >= sh->f_lo && af <= sh->f_hi;
+    };
+    int64_t m_lo = 0, m_hi = n / 2;
+    {
+        const double g = std::floor(sh->f_lo / sh->df);
+        m_lo = g > 2.0 ? (g > (double)m_hi ? m_hi : (int64_t)g - 2) : 0;
+        while (m_lo <= m_hi && (double)m_lo * sh->df < sh->f_lo) m_lo++;
+        const double t = std::ceil(sh->f_hi / sh->df);
+        if (t < (double)m_hi - 2.0) m_hi = (int64_t)t + 2;
+        while (m_hi >= m_lo && (double)m_hi * sh->df > sh->f_hi) m_hi--;
     }
-    if (band.empty()) return set_err(ILE_E_INVALID, "no grid frequency inside the band");
-    const int64_t n_band = (int64_t)band.size();
+    if (m_lo > m_hi) return set_err(ILE_E_INVALID, "no grid frequency inside the band");
+    const int64_t n_half = m_hi - m_lo + 1;
+    const int64_t n_band = 2 * n_half - (m_lo == 0 ? 1 : 0) - (2 * m_hi == n ? 1 : 0);
     const int64_t cols = (int64_t)sh->n_points * sh->n_det * sh->n_modes;
     int radix = 0;
     if (sh->route != ILE_QV_DIRECT) {
@@ -174,45 +182,60 @@ extern "C" ile_status ile_overlaps(ile_ctx *ctx, const ile_qv_shape *sh, const v
             return set_err(ILE_E_INVALID, "decimated route needs a radix in {2, 4, 8, 16} dividing n_freq that "
                                           "puts the window on at most 64 decimated times");
     }
-    auto plan = [&](int r, int &ns_, size_t &need_) {
-        ns_ = r ? qv_dec_slices(n, cols, sh->n_time, sh->win_half, r) : qv_slices(n_band, cols, sh->n_time);
-        need_ = r ? qv_dec_scratch_bytes(n, n_band, cols, sh->n_time, sh->win_half, r, ns_)
-                  : qv_scratch_bytes(n, n_band, cols, sh->n_time, ns_);
+    // the automatic route's order: windowed FFT, decimated, direct; a route
+    // whose scratch cannot be allocated within the budget gives way to the next
+    bool win = sh->route == ILE_QV_AUTO && qv_win_ok(n, n_band, sh->n_time);
+    auto plan = [&](bool w, int r, int &ns_, size_t &need_) {
+        ns_ = w ? 1 : r ? qv_dec_slices(n, cols, sh->n_time, sh->win_half, r) : qv_slices(n_band, cols, sh->n_time);
+        need_ = w   ? qv_win_scratch_bytes(n, n_half, sh->n_modes, sh->n_det, sh->n_points, sh->n_time)
+                : r ? qv_dec_scratch_bytes(n, cols, sh->n_time, sh->win_half, r, ns_)
+                    : qv_scratch_bytes(n, n_band, cols, sh->n_time, ns_);
     };
     int ns = 0;
     size_t need = 0;
-    plan(radix, ns, need);
     void *scratch = nullptr;
-    const std::string prev_err = ile_last_error();   // kept if the fallback succeeds
-    s = ctx_alloc(ctx, &scratch, need, "overlap scratch");
-    if (s != ILE_OK && radix && sh->route == ILE_QV_AUTO) {
-        // the decimated route's partial sums (n per column) do not fit where
-        // the direct route's X (n_band per column) may: take the direct route
-        radix = 0;
-        plan(radix, ns, need);
+    const std::string prev_err = ile_last_error();   // kept if a fallback succeeds
+    for (;;) {
+        plan(win, radix, ns, need);
         s = ctx_alloc(ctx, &scratch, need, "overlap scratch");
-        if (s == ILE_OK) set_err(ILE_OK, prev_err);
+        if (s == ILE_OK || sh->route != ILE_QV_AUTO) break;
+        if (win)
+            win = false;
+        else if (radix)
+            radix = 0;
+        else
+            break;
     }
     if (s != ILE_OK) return s;
-    // the band lists go through pinned staging, so that nothing in the call
-    // waits for the stream before the final synchronisation
-    const size_t stage_bytes = (size_t)n_band * (radix ? 8 : 16);
-    char *stage = (char *)pin_alloc(ctx, stage_bytes);
-    if (!stage) {
-        ctx_free(ctx, scratch, need);
-        return set_err(ILE_E_NOMEM, "pinned staging");
-    }
-    std::memcpy(stage, band.data(), (size_t)n_band * 8);
+    set_err(ILE_OK, prev_err);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (radix) {
+    char *stage = nullptr;
+    const size_t stage_bytes = (size_t)n_band * 16;
+    if (win) {
+        e = launch_qv_win(hlm, data, inv_psd, n, sh->n_modes, sh->n_det, sh->n_points, sh->df, m_lo, n_half,
+                          sh->n_time, sh->win_half, Q, U, V, scratch, st);
+    } else if (radix) {
         e = launch_qv_dec(hlm, data, inv_psd, n, sh->n_modes, sh->n_det, sh->n_points, sh->df, sh->f_lo, sh->f_hi,
-                          (const int64_t *)stage, n_band, sh->n_time, sh->win_half, radix, Q, U, V, scratch, ns, st);
+                          m_lo, n_half, sh->n_time, sh->win_half, radix, Q, U, V, scratch, ns, st);
     } else {
-        std::memcpy(stage + (size_t)n_band * 8, msig.data(), (size_t)n_band * 8);
-        e = launch_qv(hlm, data, inv_psd, n, sh->n_modes, sh->n_det, sh->n_points, sh->df, (const int64_t *)stage,
-                      (const int64_t *)(stage + (size_t)n_band * 8), n_band, sh->n_time, sh->win_half, Q, U, V,
-                      scratch, ns, st);
+        // the direct route's band lists go through pinned staging, so that
+        // nothing in the call waits for the stream before the final
+        // synchronisation
+        stage = (char *)pin_alloc(ctx, stage_bytes);
+        if (!stage) {
+            ctx_free(ctx, scratch, need);
+            return set_err(ILE_E_NOMEM, "pinned staging");
+        }
+        int64_t *band = (int64_t *)stage, *msig = band + n_band, q = 0;
+        for (int64_t m = 0; m < n; m++) {
+            const int64_t ms = m < (n + 1) / 2 ? m : m - n;   // FFT-order signed index
+            if (!on(ms)) continue;
+            band[q] = m;
+            msig[q++] = ms;
+        }
+        e = launch_qv(hlm, data, inv_psd, n, sh->n_modes, sh->n_det, sh->n_points, sh->df, band, msig, n_band, m_lo,
+                      n_half, sh->n_time, sh->win_half, Q, U, V, scratch, ns, st);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);   // the staging and the scratch are released below
     else (void)hipStreamSynchronize(st);

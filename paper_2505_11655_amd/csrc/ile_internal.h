@@ -513,8 +513,8 @@ hipError_t launch_ac_update(int policy, const AcJob *d_jobs, const AcJob *h_jobs
 int qv_slices(int64_t n_band, int64_t cols, int n_time);
 size_t qv_scratch_bytes(int64_t n, int64_t n_band, int64_t cols, int n_time, int n_slices);
 hipError_t launch_qv(const void *hlm, const void *data, const double *inv_psd, int64_t n, int na, int nd, int np,
-                     double df, const int64_t *h_band, const int64_t *h_msig, int64_t n_band, int n_time,
-                     int win_half, void *Q, void *U, void *V, void *scratch, int n_slices, hipStream_t st);
+                     double df, const int64_t *h_band, const int64_t *h_msig, int64_t n_band, int64_t m_lo,
+                     int64_t n_half, int n_time, int win_half, void *Q, void *U, void *V, void *scratch, int n_slices, hipStream_t st);
 
 // Order-preserving integer keys of finite values (key(a) < key(b) iff
 // a < b; -0 is taken as +0), their inverse, and the fixed-point sample mass

@@ -1,5 +1,7 @@
-// The decimated route for Q of eq. (QUV) (k_qv.hip); the direct route's
-// launcher is declared with the other kernels.
+// The windowed-FFT and the decimated route for Q of eq. (QUV) (k_qv.hip); the
+// direct route's launcher is declared with the other kernels.  Every route
+// takes the band as the bins m_lo .. m_lo + n_half - 1 (0 <= m <= n / 2) and
+// their mirrors n - m.
 #pragma once
 #include <cstdint>
 #include <hip/hip_runtime.h>
@@ -14,19 +16,26 @@ namespace ile {
 // when that cost exceeds the direct sum's.
 int qv_radix(int64_t n, int64_t n_band, int n_time, int win_half, bool force);
 
+// Whether the windowed-FFT route applies (n a multiple of its 512-point
+// transforms) and its estimated cost is below the direct sum's; its scratch;
+// Q by this route, U and V.
+bool qv_win_ok(int64_t n, int64_t n_band, int n_time);
+size_t qv_win_scratch_bytes(int64_t n, int64_t n_half, int na, int nd, int np, int n_time);
+hipError_t launch_qv_win(const void *hlm, const void *data, const double *inv_psd, int64_t n, int na, int nd, int np,
+                         double df, int64_t m_lo, int64_t n_half, int n_time, int win_half, void *Q, void *U, void *V,
+                         void *scratch, hipStream_t st);
+
 // Band slices of the decimated route's matrix-core stage and its scratch
-// (twiddles, band list, the radix-R partial sums and the slice partials,
-// each 256-byte aligned).
+// (twiddles, the radix-R partial sums and the slice partials, each 256-byte
+// aligned).
 int qv_dec_slices(int64_t n, int64_t cols, int n_time, int win_half, int radix);
-size_t qv_dec_scratch_bytes(int64_t n, int64_t n_band, int64_t cols, int n_time, int win_half, int radix,
-                            int n_slices);
+size_t qv_dec_scratch_bytes(int64_t n, int64_t cols, int n_time, int win_half, int radix, int n_slices);
 
 // Q (decimated route), U and V.  The band is f_lo <= |m' df| <= f_hi (m' the
-// signed index), tested on the device with the host's expression; h_band:
-// host list of its grid indices (pinned, so the upload is asynchronous).
+// signed index), tested on the device with the host's expression.
 hipError_t launch_qv_dec(const void *hlm, const void *data, const double *inv_psd, int64_t n, int na, int nd,
-                         int np, double df, double f_lo, double f_hi, const int64_t *h_band, int64_t n_band,
-                         int n_time, int win_half, int radix, void *Q, void *U, void *V, void *scratch,
+                         int np, double df, double f_lo, double f_hi, int64_t m_lo, int64_t n_half, int n_time,
+                         int win_half, int radix, void *Q, void *U, void *V, void *scratch,
                          int n_slices, hipStream_t st);
 
 }  // namespace ile

@@ -28,6 +28,8 @@
 // route's matrix-core product over N2 bins, R columns per column and only
 // the decimated times p of the window (at most 64: one time tile).  Every
 // factor is a table value at an exact integer index.
+#include <type_traits>
+
 #include "ile_internal.h"
 #include "k_qv.h"
 
@@ -411,14 +413,33 @@ __global__ void k_qv_dec_reduce(const double2 *__restrict__ part, int n_slices, 
 }
 
 // U and V: a block per (point, band slice, detector group of up to kUvDet,
-// pair group of up to kQvThreads pairs a <= b).  The block stages chunks of
-// its band slice in LDS: h_a(f) and h_a(-f) of every mode and w_k(f) of its
-// detectors.  Each thread accumulates one pair for all the group's detectors
-// over every G-th bin of a chunk (G bin lanes per pair); the lanes are summed
-// in lane order, and the slices in slice order by k_qv_uv_sum (with one slice
-// the block writes U and V itself).  Deterministic for a given launch shape.
+// pair group of up to kQvThreads pairs a <= b).  The band is symmetric in f, so
+// a slice is a run of bins m >= 0 and each bin stands for f and -f: the block
+// stages chunks of its slice in LDS, h_a(f) and h_a(-f) of every mode and
+// w_k(f), w_k(-f) of its detectors, and every staged value serves both
+//   U: w(f) conj(h_a(f)) h_b(f) + w(-f) conj(h_a(-f)) h_b(-f),
+//   V: w(f) h_a(-f) h_b(f) + w(-f) h_a(f) h_b(-f)
+// (a bin that is its own mirror, m = 0 or n / 2, has w(-f) = 0 here), which
+// halves the reads of the modes against a pass over both signs.  The rows of
+// the chunk are one element longer than it, so that the lanes of a wave, on
+// different rows at one bin, fall on different banks.  Each thread
+// accumulates a strip of up to three pairs (a, b), (a, b + 1), (a, b + 2) for
+// all the group's detectors over every G-th bin of a chunk (G bin lanes per
+// strip): 11 LDS reads for three pairs where one pair alone takes 7.  The
+// lanes are summed in lane order, and the slices in slice order by
+// k_qv_uv_sum (with one slice the block writes U and V itself).
+// Deterministic for a given launch shape.  Bounded by the vector unit and the
+// LDS reads together.
+// Measured, 256 points x 9 modes x 3 detectors x 8,034 band bins: 0.17 ms;
+// 0.32 ms with one pair per thread and a pass over both signs.
 constexpr int kUvDet = 4;
-constexpr int kUvChunk = 128;  // bins per LDS chunk (fewer for many modes)
+constexpr int kUvChunk = 128;  // most bins per LDS chunk (a power of two, fewer for many modes)
+constexpr int kUvStrip = 3;    // pairs per thread
+__host__ __device__ inline int uv_strips(int na) {
+    int q = 0;
+    for (int a = 0; a < na; a++) q += (na - a + kUvStrip - 1) / kUvStrip;
+    return q;
+}
 
 __device__ __forceinline__ void uv_pair(int q, int na, int &a, int &b) {
     a = 0;
@@ -438,90 +459,131 @@ __device__ __forceinline__ void uv_store(double2 *U, double2 *V, int64_t base, i
     V[base + b * na + a] = make_double2(f * s[2], f * s[3]);
 }
 
+template <int ND>
 __global__ void __launch_bounds__(kQvThreads)
-    k_qv_uv(const double2 *__restrict__ hlm, const double *__restrict__ inv_psd, const int64_t *__restrict__ band,
-            int64_t n_band, int64_t n, int na, int nd, double df, int64_t slice, int n_sl, int cb, int n_dg,
+    k_qv_uv(const double2 *__restrict__ hlm, const double *__restrict__ inv_psd, int64_t m_lo, int64_t n_half,
+            int64_t n, int na, int nd, double df, int64_t slice, int n_sl, int lcb, int n_dg, int n_strip,
             double *__restrict__ partial, double2 *__restrict__ U, double2 *__restrict__ V) {
     extern __shared__ double uv_lds[];
     const int npair = na * (na + 1) / 2;
     const int64_t p = blockIdx.x;
     const int sl = blockIdx.y;
-    const int dg = (int)(blockIdx.z % n_dg), pg = (int)(blockIdx.z / n_dg);
+    const int dg = (int)(blockIdx.z % n_dg), sg = (int)(blockIdx.z / n_dg);
     const int k0 = dg * kUvDet;
-    const int nk = nd - k0 < kUvDet ? nd - k0 : kUvDet;
-    const int pair0 = pg * kQvThreads;
-    const int np_here = npair - pair0 < kQvThreads ? npair - pair0 : kQvThreads;
-    const int G = kQvThreads / np_here;
+    const int nk = nd - k0 < ND ? nd - k0 : ND;
+    const int strip0 = sg * kQvThreads;
+    const int ns_here = n_strip - strip0 < kQvThreads ? n_strip - strip0 : kQvThreads;
+    const int G = kQvThreads / ns_here;
     const int tid = threadIdx.x;
-    const bool active = tid < np_here * G;
-    const int lp = tid % np_here, g = tid / np_here;
-    int a = 0, b = 0;
-    uv_pair(pair0 + lp, na, a, b);
-    double2 *sH = (double2 *)uv_lds;            // [na][cb]  h_a(f)
-    double2 *sM = sH + (size_t)na * cb;         // [na][cb]  h_a(-f)
-    double *sW = (double *)(sM + (size_t)na * cb);   // [kUvDet][cb]
-    double acc[kUvDet][4];
+    const bool active = tid < ns_here * G;
+    const int ls = active ? tid / G : 0, g = tid % G;   // consecutive lanes on consecutive bins of one row
+    const int cb = 1 << lcb, row = cb + 1;
+    // the strip's row a and first column b, and the pairs it holds
+    int a = 0, q = strip0 + ls;
+    while (q >= (na - a + kUvStrip - 1) / kUvStrip) {
+        q -= (na - a + kUvStrip - 1) / kUvStrip;
+        a++;
+    }
+    const int b = a + kUvStrip * q;
+    const int nb = na - b < kUvStrip ? na - b : kUvStrip;
+    double2 *sH = (double2 *)uv_lds;            // [na][row]  h_a(f)
+    double2 *sM = sH + (size_t)na * row;        // [na][row]  h_a(-f)
+    double2 *sW = sM + (size_t)na * row;        // [ND][row]  w_k(f), w_k(-f)
+    double acc[kUvStrip][ND][4];
 #pragma unroll
-    for (int kk = 0; kk < kUvDet; kk++)
+    for (int t = 0; t < kUvStrip; t++)
 #pragma unroll
-        for (int c = 0; c < 4; c++) acc[kk][c] = 0.0;
+        for (int kk = 0; kk < ND; kk++)
+#pragma unroll
+            for (int c = 0; c < 4; c++) acc[t][kk][c] = 0.0;
     const int64_t e_lo = (int64_t)sl * slice;
-    const int64_t e_hi = e_lo + slice < n_band ? e_lo + slice : n_band;
+    const int64_t e_hi = e_lo + slice < n_half ? e_lo + slice : n_half;
+    const double2 *hp = hlm + p * na * n;
     for (int64_t eb = e_lo; eb < e_hi; eb += cb) {
         const int ncb = e_hi - eb < cb ? (int)(e_hi - eb) : cb;
         __syncthreads();
-        for (int s = tid; s < na * ncb; s += kQvThreads) {
-            const int am = s / ncb, c = s % ncb;
-            const int64_t m = band[eb + c];
-            const int64_t mn = m == 0 ? 0 : n - m;
-            const double2 *h = hlm + (p * na + am) * n;
-            sH[am * cb + c] = h[m];
-            sM[am * cb + c] = h[mn];
+        if (lcb >= 6) {
+            // straight to LDS, 64 bins of one row per wave instruction, all in
+            // flight at once (a bin past the chunk loads its first bin, unused)
+            const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), per = 1 << (lcb - 6);
+            for (int e = wv; e < 2 * na * per; e += kQvThreads / 64) {
+                const int c = 64 * (e & (per - 1)) + lane, r = e >> (lcb - 6), am = r >> 1;
+                const int64_t m = m_lo + eb + (c < ncb ? c : 0);
+                const double2 *src = hp + (int64_t)am * n + ((r & 1) && m > 0 ? n - m : m);
+                double2 *dst = ((r & 1) ? sM : sH) + am * row + 64 * (e & (per - 1));
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                                 (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+            }
+        } else {
+            for (int e = tid; e < na << lcb; e += kQvThreads) {
+                const int am = e >> lcb, c = e & (cb - 1);
+                const int64_t m = m_lo + eb + (c < ncb ? c : 0);
+                sH[am * row + c] = hp[(int64_t)am * n + m];
+                sM[am * row + c] = hp[(int64_t)am * n + (m > 0 ? n - m : 0)];
+            }
         }
-        for (int s = tid; s < nk * ncb; s += kQvThreads) {
-            const int kk = s / ncb, c = s % ncb;
-            sW[kk * cb + c] = inv_psd ? inv_psd[(int64_t)(k0 + kk) * n + band[eb + c]] : 1.0;
+        for (int e = tid; e < nk << lcb; e += kQvThreads) {
+            const int kk = e >> lcb, c = e & (cb - 1);
+            const int64_t m = m_lo + eb + (c < ncb ? c : 0);
+            const bool own = m == 0 || 2 * m == n;
+            const double *w = inv_psd ? inv_psd + (int64_t)(k0 + kk) * n : nullptr;
+            sW[kk * row + c] = make_double2(w ? w[m] : 1.0, own ? 0.0 : (w ? w[n - m] : 1.0));
         }
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's loads have reached LDS
         __syncthreads();
         if (active) {
             for (int c = g; c < ncb; c += G) {
-                const double2 x = sH[a * cb + c], y = sH[b * cb + c], z = sM[a * cb + c];
-                const double p0 = x.x * y.x + x.y * y.y, p1 = x.x * y.y - x.y * y.x;   // conj(h_a) h_b
-                const double p2 = z.x * y.x - z.y * y.y, p3 = z.x * y.y + z.y * y.x;   // h_a(-f) h_b
+                const double2 x = sH[a * row + c], z = sM[a * row + c];   // f, -f
+                double2 w[ND];
 #pragma unroll
-                for (int kk = 0; kk < kUvDet; kk++) {
-                    if (kk < nk) {
-                        const double w = sW[kk * cb + c];
-                        acc[kk][0] += w * p0;
-                        acc[kk][1] += w * p1;
-                        acc[kk][2] += w * p2;
-                        acc[kk][3] += w * p3;
+                for (int kk = 0; kk < ND; kk++)
+                    if (kk < nk) w[kk] = sW[kk * row + c];
+#pragma unroll
+                for (int s = 0; s < kUvStrip; s++) {
+                    if (s >= nb) break;
+                    const double2 y = sH[(b + s) * row + c], t = sM[(b + s) * row + c];
+                    const double p0 = x.x * y.x + x.y * y.y, p1 = x.x * y.y - x.y * y.x;   // conj(h_a) h_b at f
+                    const double p2 = z.x * y.x - z.y * y.y, p3 = z.x * y.y + z.y * y.x;   // h_a(-f) h_b(f)
+                    const double q0 = z.x * t.x + z.y * t.y, q1 = z.x * t.y - z.y * t.x;   // the same, f -> -f
+                    const double q2 = x.x * t.x - x.y * t.y, q3 = x.x * t.y + x.y * t.x;
+#pragma unroll
+                    for (int kk = 0; kk < ND; kk++) {
+                        if (kk < nk) {
+                            acc[s][kk][0] = fma(w[kk].y, q0, fma(w[kk].x, p0, acc[s][kk][0]));
+                            acc[s][kk][1] = fma(w[kk].y, q1, fma(w[kk].x, p1, acc[s][kk][1]));
+                            acc[s][kk][2] = fma(w[kk].y, q2, fma(w[kk].x, p2, acc[s][kk][2]));
+                            acc[s][kk][3] = fma(w[kk].y, q3, fma(w[kk].x, p3, acc[s][kk][3]));
+                        }
                     }
                 }
             }
         }
     }
-    // bin lanes summed in lane order
-    __syncthreads();
-    double *red = uv_lds;   // [kQvThreads][kUvDet * 4]
+    // bin lanes summed in lane order, one pair of the strips at a time
+    double *red = uv_lds;   // [kQvThreads][ND * 4]
 #pragma unroll
-    for (int kk = 0; kk < kUvDet; kk++)
+    for (int s = 0; s < kUvStrip; s++) {
+        __syncthreads();
 #pragma unroll
-        for (int c = 0; c < 4; c++) red[tid * kUvDet * 4 + kk * 4 + c] = acc[kk][c];
-    __syncthreads();
-    if (!active || g != 0) return;
-    for (int kk = 0; kk < nk; kk++) {
-        double s[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int gg = 0; gg < G; gg++)
+        for (int kk = 0; kk < ND; kk++)
 #pragma unroll
-            for (int c = 0; c < 4; c++) s[c] += red[(gg * np_here + lp) * kUvDet * 4 + kk * 4 + c];
-        const int64_t pk = p * nd + k0 + kk;
-        if (n_sl == 1) {
-            uv_store(U, V, pk * na * na, na, a, b, 2.0 * df, s);
-        } else {
-            double *o = partial + ((pk * npair + pair0 + lp) * n_sl + sl) * 4;
+            for (int c = 0; c < 4; c++) red[tid * ND * 4 + kk * 4 + c] = acc[s][kk][c];
+        __syncthreads();
+        if (!active || g != 0 || s >= nb) continue;
+        for (int kk = 0; kk < nk; kk++) {
+            double t[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int gg = 0; gg < G; gg++)
 #pragma unroll
-            for (int c = 0; c < 4; c++) o[c] = s[c];
+                for (int c = 0; c < 4; c++) t[c] += red[(ls * G + gg) * ND * 4 + kk * 4 + c];
+            const int64_t pk = p * nd + k0 + kk;
+            if (n_sl == 1) {
+                uv_store(U, V, pk * na * na, na, a, b + s, 2.0 * df, t);
+            } else {
+                const int pair = a * na - a * (a - 1) / 2 + (b + s - a);
+                double *o = partial + ((pk * npair + pair) * n_sl + sl) * 4;
+#pragma unroll
+                for (int c = 0; c < 4; c++) o[c] = t[c];
+            }
         }
     }
 }
@@ -544,28 +606,305 @@ __global__ void k_qv_uv_sum(const double *__restrict__ partial, int64_t n_pk, in
 }
 
 // U and V (k_qv_uv, then k_qv_uv_sum over its band slices): band slices so
-// that the grid has about 1024 blocks, the slice partials held in `part`
-// (part_bytes long; free once Q has been reduced from it).
-void launch_uv(const void *hlm, const double *inv_psd, const int64_t *band, int64_t n_band, int64_t n, int na,
-               int nd, int np, double df, double *part, int64_t part_bytes, void *U, void *V, hipStream_t st) {
+// that the grid is one round of resident blocks (three to a CU by LDS), at
+// least one chunk and at most 32 of them, the slice partials held in `part`
+// (part_bytes long; free once Q has been reduced from it).  The band is the
+// bins m_lo .. m_lo + n_half - 1 and their mirrors.
+struct UvPlan {
+    int n_dg, n_sg, n_strip, lcb, n_sl;   // lcb: log2 of the chunk's bins
+    int64_t per_sl;                       // bytes of one slice's partials
+};
+UvPlan uv_plan(int64_t n_half, int na, int nd, int np) {
+    UvPlan u;
     const int npair = na * (na + 1) / 2;
-    const int n_dg = (nd + kUvDet - 1) / kUvDet;
-    const int n_pg = (npair + kQvThreads - 1) / kQvThreads;
-    const int cb = (int)std::max<int64_t>(1, std::min<int64_t>(kUvChunk, 49152 / ((int64_t)na * 32 + kUvDet * 8)));
-    const int64_t blocks1 = (int64_t)np * n_dg * n_pg;
-    int64_t n_sl = std::max<int64_t>(1, std::min<int64_t>((1024 + blocks1 - 1) / blocks1, (n_band + 4 * cb - 1) / (4 * cb)));
-    const int64_t per_sl = (int64_t)np * nd * npair * 32;
-    n_sl = std::min<int64_t>(n_sl, std::max<int64_t>(1, part_bytes / per_sl));
-    const int64_t uslice = (n_band + n_sl - 1) / n_sl;
-    n_sl = (n_band + uslice - 1) / uslice;
-    const size_t lds = std::max<size_t>((size_t)cb * ((size_t)na * 32 + kUvDet * 8), (size_t)kQvThreads * kUvDet * 4 * 8);
-    hipLaunchKernelGGL(k_qv_uv, dim3((unsigned)np, (unsigned)n_sl, (unsigned)(n_dg * n_pg)), dim3(kQvThreads), lds, st,
-                       (const double2 *)hlm, inv_psd, band, n_band, n, na, nd, df, uslice, (int)n_sl, cb, n_dg,
-                       part, (double2 *)U, (double2 *)V);
+    u.n_dg = (nd + kUvDet - 1) / kUvDet;
+    u.n_strip = uv_strips(na);
+    u.n_sg = (u.n_strip + kQvThreads - 1) / kQvThreads;
+    u.lcb = 0;
+    while ((2 << u.lcb) <= kUvChunk && ((int64_t)(2 << u.lcb) + 1) * ((int64_t)na * 32 + kUvDet * 16) <= 49152) u.lcb++;
+    const int64_t cb = (int64_t)1 << u.lcb, blocks1 = (int64_t)np * u.n_dg * u.n_sg;
+    u.n_sl = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(768 / blocks1, 32), (n_half + cb - 1) / cb));
+    u.per_sl = (int64_t)np * nd * npair * 32;
+    return u;
+}
+void launch_uv(const void *hlm, const double *inv_psd, int64_t m_lo, int64_t n_half, int64_t n, int na, int nd, int np,
+               double df, double *part, int64_t part_bytes, void *U, void *V, hipStream_t st) {
+    const int npair = na * (na + 1) / 2;
+    const UvPlan u = uv_plan(n_half, na, nd, np);
+    int64_t n_sl = std::min<int64_t>(u.n_sl, std::max<int64_t>(1, part_bytes / u.per_sl));
+    const int64_t uslice = (n_half + n_sl - 1) / n_sl;
+    n_sl = (n_half + uslice - 1) / uslice;
+    const size_t lds = std::max<size_t>((((size_t)1 << u.lcb) + 1) * ((size_t)na * 32 + kUvDet * 16),
+                                        (size_t)kQvThreads * kUvDet * 4 * 8);
+    // accumulators for as many detectors as a group holds
+    auto go = [&](auto ND_) {
+        hipLaunchKernelGGL(k_qv_uv<decltype(ND_)::value>, dim3((unsigned)np, (unsigned)n_sl, (unsigned)(u.n_dg * u.n_sg)),
+                           dim3(kQvThreads), lds, st, (const double2 *)hlm, inv_psd, m_lo, n_half, n, na, nd, df, uslice,
+                           (int)n_sl, u.lcb, u.n_dg, u.n_strip, part, (double2 *)U, (double2 *)V);
+    };
+    if (nd <= 2)
+        go(std::integral_constant<int, 2>{});
+    else if (nd == 3)
+        go(std::integral_constant<int, 3>{});
+    else
+        go(std::integral_constant<int, 4>{});
     if (n_sl > 1) {
         const int64_t ue = (int64_t)np * nd * npair;
         hipLaunchKernelGGL(k_qv_uv_sum, dim3((unsigned)std::min<int64_t>((ue + 255) / 256, 65536)), dim3(256), 0, st,
                            part, (int64_t)np * nd, na, (int)n_sl, df, (double2 *)U, (double2 *)V);
+    }
+}
+
+// --------------------------------------------------------- windowed FFT route
+// Q over the window as M = n / 512 transforms of 512 points each: with the
+// window in blocks of 512 times, j = 512 blk - win_half + i (0 <= i < 512),
+// and the grid index m = M m2 + m1 (0 <= m2 < 512, 0 <= m1 < M),
+//   e^{2 pi i m j / n} = e^{2 pi i m (512 blk - win_half) / n} e^{2 pi i m2 i / 512} e^{2 pi i m1 i / n},
+//   Q(j) = sum_m1 zeta_i^m1 FFT512[ conj(h)(M m2 + m1) D(M m2 + m1) ](i),  zeta_i = e^{2 pi i i / n},
+// with D = 2 df d w e^{2 pi i m (512 blk - win_half) / n} on the band, 0 off it
+// (k_qv_wprep, once per call).  The sum over m1 is Horner's rule with the
+// factor zeta_i^4 (the four waves of a block take m1 mod 4), so nothing but
+// the window is ever written: the radix stage of the decimated route writes
+// and reads n elements per column.  Work per column and bin: 9 radix-2 stages
+// of a 512-point transform (three radix-8 steps in registers) against a
+// 32-row matrix product over every bin.
+// One wave holds one transform, 8 points per lane: step 1 over r of m2 =
+// 64 r + l, step 2 over a and step 3 over b of l = 8 a + b, output
+// i = k + 8 k2 + 64 k3.  Between the steps the real and then the imaginary
+// parts change lanes through 576 doubles of LDS; the strides 72 and 9 keep
+// every access conflict-free.  A block is one column; it stages h, kWinC
+// consecutive m1 of every m2 at a time (runs of 64 bytes), straight into LDS.
+// The blocks of one mode row's detectors are neighbours on one XCD, so that
+// its L2 serves all but the first.  Small blocks (one wave per SIMD) so that
+// three fit a CU by registers and LDS and one's staging hides behind the
+// others' transforms: a block of two waves for each of three detectors, which
+// reads h once, ran one to a CU (518 us on the shape below).
+// Measured, 256 points x 9 modes x 3 detectors on 16,384 bins (20-1024 Hz, 410
+// window times): 0.32 ms where the radix stage, the product and the slice sum
+// of the decimated route take 1.36 ms.  The vector unit and the LDS are each
+// busy about 55 % of it.
+constexpr int kWinP = 512;
+constexpr int kWinC = 4;                   // m1 per staged chunk, and waves per block
+constexpr int kWinSlab = 64 * kWinC;       // staged elements of 64 m2
+constexpr int kWinThreads = 64 * kWinC;
+constexpr int kWinX = 576;                 // exchange buffer of a wave (doubles)
+// Cost per bin, column and window block in the unit of dec_cost (a complex
+// product of the matrix-core kernel): 0.32 ms for 6,912 columns of 16,384
+// bins, where the direct sum's 497 per band bin (8,034) take 4.0 ms.
+constexpr int kWinCost = 20;
+
+__device__ __forceinline__ double2 cmul(double2 x, double2 w) {
+    return make_double2(x.x * w.x - x.y * w.y, x.x * w.y + x.y * w.x);
+}
+
+// tw[r] = e^{2 pi i r / n}, and D[blk][k][m1][m2].
+__global__ void __launch_bounds__(kQvThreads)
+    k_qv_wprep(const double2 *__restrict__ data, const double *__restrict__ inv_psd, int64_t n, int nd, double df,
+               int64_t m_lo, int64_t m_hi, int win_half, double2 *__restrict__ tw, double2 *__restrict__ D) {
+    const int64_t M = n / kWinP;
+    const int k = blockIdx.y, blk = blockIdx.z;
+    for (int64_t e = (int64_t)blockIdx.x * kQvThreads + threadIdx.x; e < n; e += (int64_t)gridDim.x * kQvThreads) {
+        double s, c;
+        if (k == 0 && blk == 0) {
+            sincospi(2.0 * (double)e / (double)n, &s, &c);
+            tw[e] = make_double2(c, s);
+        }
+        const int64_t m = M * (e % kWinP) + e / kWinP;
+        const int64_t mm = 2 * m > n ? n - m : m;   // |signed index|
+        double2 v = make_double2(0.0, 0.0);
+        if (mm >= m_lo && mm <= m_hi) {
+            int64_t r = (m * ((int64_t)kWinP * blk - win_half)) % n;
+            r = r < 0 ? r + n : r;
+            sincospi(2.0 * (double)r / (double)n, &s, &c);
+            const double w = 2.0 * df * (inv_psd ? inv_psd[(int64_t)k * n + m] : 1.0);
+            const double2 d = data[(int64_t)k * n + m];
+            v = cmul(make_double2(d.x * w, d.y * w), make_double2(c, s));
+        }
+        D[((int64_t)blk * nd + k) * n + e] = v;
+    }
+}
+
+// v[k] <- sum_j v[j] e^{2 pi i j k / 8}
+__device__ __forceinline__ void dft8(double2 (&v)[8]) {
+    constexpr double h = 0.70710678118654752440;
+    auto add = [](double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); };
+    auto sub = [](double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); };
+    auto rot = [](double2 a) { return make_double2(-a.y, a.x); };   // i a
+    const double2 a0 = add(v[0], v[4]), a1 = sub(v[0], v[4]), a2 = add(v[2], v[6]), a3 = rot(sub(v[2], v[6]));
+    const double2 a4 = add(v[1], v[5]), a5 = sub(v[1], v[5]), a6 = add(v[3], v[7]), a7 = rot(sub(v[3], v[7]));
+    const double2 b0 = add(a0, a2), b2 = sub(a0, a2), b1 = add(a1, a3), b3 = sub(a1, a3);
+    const double2 c0 = add(a4, a6), c2 = rot(sub(a4, a6)), o1 = add(a5, a7), o3 = sub(a5, a7);
+    const double2 c1 = make_double2((o1.x - o1.y) * h, (o1.x + o1.y) * h);      // e^{i pi / 4} o1
+    const double2 c3 = make_double2((-o3.x - o3.y) * h, (o3.x - o3.y) * h);     // e^{3 i pi / 4} o3
+    v[0] = add(b0, c0);
+    v[4] = sub(b0, c0);
+    v[2] = add(b2, c2);
+    v[6] = sub(b2, c2);
+    v[1] = add(b1, c1);
+    v[5] = sub(b1, c1);
+    v[3] = add(b3, c3);
+    v[7] = sub(b3, c3);
+}
+
+// Lanes of one wave exchange through LDS: its accesses stay in program order
+// on either side (the LDS serves one wave's instructions in order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// v[j] of lane w0 + j ws is written, v[j] is read from r0 + j rs (both parts
+// through the same doubles, one after the other).
+template <int WS, int RS>
+__device__ __forceinline__ void wave_exchange(double2 (&v)[8], double *x, int w0, int r0) {
+#pragma unroll
+    for (int j = 0; j < 8; j++) x[w0 + j * WS] = v[j].x;
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j].x = x[r0 + j * RS];
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < 8; j++) x[w0 + j * WS] = v[j].y;
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j].y = x[r0 + j * RS];
+    wave_sync();
+}
+
+// Block: column (p, a, k) x window block x m1 slice.  slabs: bit r is set when
+// some bin with m2 in [64 r, 64 r + 64) is on the band; the staging area holds
+// those slabs only.  out: [slice][col][n_time].
+__global__ void __launch_bounds__(kWinThreads, 4)
+    k_qv_win(const double2 *__restrict__ hlm, const double2 *__restrict__ D, const double2 *__restrict__ tw, int64_t n,
+             int na, int nd, int64_t n_pa, int n_blk, int n_sl, int64_t m1_per, int64_t m_lo, int64_t m_hi, int slabs,
+             int n_time, double2 *__restrict__ out) {
+    extern __shared__ __align__(16) double2 win_lds[];
+    const int64_t M = n / kWinP;
+    // blocks of one mode row run on one XCD and share its L2
+    const int64_t nb = gridDim.x, hb = blockIdx.x;
+    int64_t lid = nb % 8 == 0 ? (hb % 8) * (nb / 8) + hb / 8 : hb;
+    const int k = (int)(lid % nd);
+    lid /= nd;
+    const int sl = (int)(lid % n_sl);
+    lid /= n_sl;
+    const int blk = (int)(lid % n_blk);
+    const int64_t pa = lid / n_blk;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_slab = __popc(slabs);
+    // [exchange buffers][step-2 twiddles][staged slabs], the twiddles
+    // e^{2 pi i b k2 / 64} at [k2][b]
+    double *xb = (double *)win_lds + wv * kWinX;
+    double2 *sT = win_lds + kWinC * (kWinX / 2);
+    double2 *sH = sT + 64;
+    const double2 *h = hlm + pa * n;
+    const double2 *Dk = D + ((int64_t)blk * nd + k) * n;
+    const int i0 = (lane >> 3) + 8 * (lane & 7);                       // output i = i0 + 64 k3
+    if (wv == 0) sT[lane] = tw[(int64_t)(lane & 7) * (lane >> 3) * 8 * M];
+    // zeta_i^4 = z0 zc[k3] (i = i0 + 64 k3): a lane factor and a uniform one,
+    // the latter in scalar registers
+    auto mod_n = [&](int64_t r) {   // of an index below 4 n
+        while (r >= n) r -= n;
+        return r;
+    };
+    const double2 z0 = tw[mod_n(kWinC * i0)];
+    double2 t1[8], zc[8], acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        if (j > 0) t1[j] = tw[(int64_t)lane * j * M];             // e^{2 pi i l k / 512}
+        if (j > 0) zc[j] = tw[mod_n(kWinC * 64 * j)];
+        acc[j] = make_double2(0.0, 0.0);
+    }
+    // this lane's staged m1 of a chunk and M m2 of the first slab (n < 2^31)
+    const unsigned m2l = 16 * wv + (lane >> 2), m1x = (lane & 3) ^ ((m2l >> 1) & 3), mb = (unsigned)M * m2l;
+    const unsigned m_w = (unsigned)(m_hi - m_lo);
+    const int64_t s_lo = (int64_t)sl * m1_per, s_hi = s_lo + m1_per < M ? s_lo + m1_per : M;
+    for (int64_t c0 = s_lo + (s_hi - s_lo - 1) / kWinC * kWinC; c0 >= s_lo; c0 -= kWinC) {
+        __syncthreads();   // the previous chunk's reads are done
+        // The chunk goes straight to LDS, all of it in flight at once, 16 m2 x
+        // 4 m1 per wave instruction.  Slot (m2, c) holds m1 = c0 +
+        // (c ^ (m2 / 2 mod 4)), so that the lanes of a transform, on
+        // consecutive m2 at one m1, read different banks.  An element off the
+        // band or past the slice is not read: its lane loads the band's first
+        // bin instead (D is zero there, and no m1 past the slice is used).
+        const unsigned m1 = (unsigned)c0 + m1x;
+        const unsigned mf = (int64_t)m1 < s_hi ? m1 + mb : ~0u;
+        int bits = slabs;
+        for (int g = 0; g < n_slab; g++, bits &= bits - 1) {
+            const unsigned m = mf + (unsigned)(64 * (__ffs(bits) - 1)) * (unsigned)M;
+            const unsigned mm = m < (unsigned)n - m ? m : (unsigned)n - m;
+            const double2 *src = h + (mf != ~0u && mm - (unsigned)m_lo <= m_w ? m : (unsigned)m_lo);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                             (__attribute__((address_space(3))) void *)(sH + g * kWinSlab + wv * 64), 16,
+                                             0, 0);
+        }
+        // the wave's row of D travels with them (a wave past the slice reads a
+        // valid row that it does not use)
+        double2 v[8];
+        const double2 *dj = Dk + (c0 + wv < s_hi ? c0 + wv : c0) * kWinP + lane;
+#pragma unroll
+        for (int r = 0; r < 8; r++) {
+            v[r] = make_double2(0.0, 0.0);
+            if ((slabs >> r) & 1) v[r] = dj[64 * r];
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's loads have reached LDS
+        __syncthreads();
+        if (c0 + wv >= s_hi) continue;
+        const double2 *hj = sH + lane * kWinC + (wv ^ ((lane >> 1) & 3));
+#pragma unroll
+        for (int r = 0; r < 8; r++)
+            if ((slabs >> r) & 1) {
+                const double2 d = v[r], x = *hj;
+                v[r] = make_double2(x.x * d.x + x.y * d.y, x.x * d.y - x.y * d.x);   // conj(h) D
+                hj += kWinSlab;
+            }
+        dft8(v);
+#pragma unroll
+        for (int q = 1; q < 8; q++) v[q] = cmul(v[q], t1[q]);
+        wave_exchange<72, 8>(v, xb, lane, (lane >> 3) * 72 + (lane & 7));
+        dft8(v);
+#pragma unroll
+        for (int q = 1; q < 8; q++) v[q] = cmul(v[q], sT[q * 8 + (lane & 7)]);
+        wave_exchange<9, 1>(v, xb, (lane >> 3) * 72 + (lane & 7), lane * 9);
+        dft8(v);
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            const double2 o = q > 0 ? cmul(acc[q], zc[q]) : acc[q];
+            acc[q].x = fma(-o.y, z0.y, fma(o.x, z0.x, v[q].x));
+            acc[q].y = fma(o.x, z0.y, fma(o.y, z0.x, v[q].y));
+        }
+    }
+    // the wave's own power of zeta_i, then the four waves summed in order
+    // through LDS (two at a time: the exchange buffers hold two waves' values)
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        const int64_t m1 = s_lo + wv < M ? s_lo + wv : 0;   // m1 i < n (a wave past the slice holds zeros)
+        acc[q] = cmul(acc[q], tw[m1 * (i0 + 64 * q)]);
+    }
+#pragma unroll
+    for (int h2 = 2; h2 > 0; h2 >>= 1) {
+        double2 *sum = win_lds + (wv & (h2 - 1)) * kWinP;
+        __syncthreads();
+        if (wv >= h2 && wv < 2 * h2) {
+#pragma unroll
+            for (int q = 0; q < 8; q++) sum[q * 64 + lane] = acc[q];
+        }
+        __syncthreads();
+        if (wv < h2) {
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                const double2 w = sum[q * 64 + lane];
+                acc[q] = make_double2(acc[q].x + w.x, acc[q].y + w.y);
+            }
+        }
+    }
+    if (wv != 0) return;
+    const int64_t p = pa / na, a = pa % na, col = (p * nd + k) * na + a, cols = n_pa * nd;
+    double2 *o = out + ((int64_t)sl * cols + col) * n_time;
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        const int t = blk * kWinP + i0 + 64 * q;
+        if (t < n_time) o[t] = acc[q];
     }
 }
 
@@ -609,8 +948,9 @@ int qv_slices(int64_t n_band, int64_t cols, int n_time) {
 }
 
 hipError_t launch_qv(const void *hlm, const void *data, const double *inv_psd, int64_t n, int na, int nd, int np,
-                     double df, const int64_t *h_band, const int64_t *h_msig, int64_t n_band, int n_time,
-                     int win_half, void *Q, void *U, void *V, void *scratch, int n_slices, hipStream_t st) {
+                     double df, const int64_t *h_band, const int64_t *h_msig, int64_t n_band, int64_t m_lo,
+                     int64_t n_half, int n_time, int win_half, void *Q, void *U, void *V, void *scratch,
+                     int n_slices, hipStream_t st) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     char *w = (char *)scratch;
     double2 *tw = (double2 *)w;
@@ -640,7 +980,7 @@ hipError_t launch_qv(const void *hlm, const void *data, const double *inv_psd, i
     const int64_t qe = cols * n_time;
     hipLaunchKernelGGL(k_qv_reduce, dim3((unsigned)std::min<int64_t>((qe + 255) / 256, 65536)), dim3(256), 0, st,
                        part, ns, cols, n_time, (double2 *)Q);
-    launch_uv(hlm, inv_psd, band, n_band, n, na, nd, np, df, (double *)part, (int64_t)ns * cols * n_time * 16, U, V,
+    launch_uv(hlm, inv_psd, m_lo, n_half, n, na, nd, np, df, (double *)part, (int64_t)ns * cols * n_time * 16, U, V,
               st);
     return hipGetLastError();
 }
@@ -695,16 +1035,16 @@ int qv_dec_slices(int64_t n, int64_t cols, int n_time, int win_half, int radix) 
     return slices_for(n / radix, (cols * radix + tc - 1) / tc);
 }
 
-size_t qv_dec_scratch_bytes(int64_t n, int64_t n_band, int64_t cols, int n_time, int win_half, int radix,
-                            int n_slices) {
+size_t qv_dec_scratch_bytes(int64_t n, int64_t cols, int n_time, int win_half, int radix, int n_slices) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     int p_lo, n_t2;
     dec_window(n_time, win_half, radix, p_lo, n_t2);
-    return al((size_t)n * 16) + al((size_t)(n / radix) * 16) + al((size_t)n_band * 8) + al((size_t)n * cols * 16) + al((size_t)n_slices * cols * radix * n_t2 * 16);
+    return al((size_t)n * 16) + al((size_t)(n / radix) * 16) + al((size_t)n * cols * 16) +
+           al((size_t)n_slices * cols * radix * n_t2 * 16);
 }
 
 hipError_t launch_qv_dec(const void *hlm, const void *data, const double *inv_psd, int64_t n, int na, int nd,
-                         int np, double df, double f_lo, double f_hi, const int64_t *h_band, int64_t n_band,
+                         int np, double df, double f_lo, double f_hi, int64_t m_lo, int64_t n_half,
                          int n_time, int win_half, int radix, void *Q, void *U, void *V, void *scratch,
                          int n_slices, hipStream_t st) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
@@ -718,13 +1058,9 @@ hipError_t launch_qv_dec(const void *hlm, const void *data, const double *inv_ps
     w += al((size_t)n * 16);
     double2 *tw2 = (double2 *)w;
     w += al((size_t)n2 * 16);
-    int64_t *band = (int64_t *)w;
-    w += al((size_t)n_band * 8);
     double2 *Y = (double2 *)w;
     w += al((size_t)n * cols * 16);
     double2 *part = (double2 *)w;
-    hipError_t e = hipMemcpyAsync(band, h_band, (size_t)n_band * 8, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_qv_twiddle, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, tw, n);
     hipLaunchKernelGGL(k_qv_twiddle, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, tw2, n2);
     const int64_t n_mt = (n2 + kDecM - 1) / kDecM;
@@ -766,8 +1102,85 @@ hipError_t launch_qv_dec(const void *hlm, const void *data, const double *inv_ps
     const int64_t qe = cols * n_time;
     hipLaunchKernelGGL(k_qv_dec_reduce, dim3((unsigned)std::min<int64_t>((qe + 255) / 256, 65536)), dim3(256), 0, st,
                        part, ns, cols, radix, n_t2, n_time, win_half, p_lo, (double2 *)Q);
-    launch_uv(hlm, inv_psd, band, n_band, n, na, nd, np, df, (double *)part, (int64_t)ns * cols2 * n_t2 * 16, U, V,
+    launch_uv(hlm, inv_psd, m_lo, n_half, n, na, nd, np, df, (double *)part, (int64_t)ns * cols2 * n_t2 * 16, U, V,
               st);
+    return hipGetLastError();
+}
+
+namespace {
+
+// m1 slices of the windowed route: about three blocks per CU, whole chunks of
+// kWinC per slice.
+struct WinPlan {
+    int n_blk, n_sl;
+    int64_t m1_per;
+};
+WinPlan win_plan(int64_t n, int64_t cols, int n_time) {
+    WinPlan w;
+    const int64_t M = n / kWinP;
+    w.n_blk = (n_time + kWinP - 1) / kWinP;
+    const int64_t blocks = cols * w.n_blk, chunks = (M + kWinC - 1) / kWinC;
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(chunks, (768 + blocks - 1) / blocks));
+    w.m1_per = (chunks + want - 1) / want * kWinC;
+    w.n_sl = (int)((M + w.m1_per - 1) / w.m1_per);
+    return w;
+}
+
+}  // namespace
+
+bool qv_win_ok(int64_t n, int64_t n_band, int n_time) {
+    if (n % kWinP != 0 || n >= ((int64_t)1 << 31)) return false;
+    const int64_t n_blk = (n_time + kWinP - 1) / kWinP;
+    return (double)kWinCost * (double)(n * n_blk) <
+           (double)((n_time + kQvTT - 1) / kQvTT * kQvTT + 49) * (double)n_band;
+}
+
+size_t qv_win_scratch_bytes(int64_t n, int64_t n_half, int na, int nd, int np, int n_time) {
+    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+    const WinPlan w = win_plan(n, (int64_t)np * na * nd, n_time);
+    const UvPlan u = uv_plan(n_half, na, nd, np);
+    const size_t part = w.n_sl > 1 ? (size_t)w.n_sl * np * nd * na * n_time * 16 : 0;
+    return al((size_t)n * 16) + al((size_t)n * nd * w.n_blk * 16) +
+           al(std::max<size_t>(part, u.n_sl > 1 ? (size_t)u.n_sl * (size_t)u.per_sl : 0));
+}
+
+hipError_t launch_qv_win(const void *hlm, const void *data, const double *inv_psd, int64_t n, int na, int nd, int np,
+                         double df, int64_t m_lo, int64_t n_half, int n_time, int win_half, void *Q, void *U, void *V,
+                         void *scratch, hipStream_t st) {
+    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+    const int64_t M = n / kWinP, n_pa = (int64_t)np * na, cols = n_pa * nd, m_hi = m_lo + n_half - 1;
+    const WinPlan w = win_plan(n, cols, n_time);
+    const UvPlan u = uv_plan(n_half, na, nd, np);
+    char *b = (char *)scratch;
+    double2 *tw = (double2 *)b;
+    b += al((size_t)n * 16);
+    double2 *D = (double2 *)b;
+    b += al((size_t)n * nd * w.n_blk * 16);
+    double2 *part = (double2 *)b;
+    // the slabs of 64 m2 that hold a bin of the band (m2 = m / M)
+    int slabs = 0;
+    for (int r = 0; r < 8; r++) {
+        const int64_t lo = M * 64 * r, hi = M * 64 * (r + 1) - 1;
+        const bool pos = lo <= m_hi && hi >= m_lo, neg = lo <= n - m_lo && hi >= n - m_hi;
+        if (pos || neg) slabs |= 1 << r;
+    }
+    const unsigned pb = (unsigned)std::min<int64_t>((n + kQvThreads - 1) / kQvThreads, 4096);
+    hipLaunchKernelGGL(k_qv_wprep, dim3(pb, (unsigned)nd, (unsigned)w.n_blk), dim3(kQvThreads), 0, st,
+                       (const double2 *)data, inv_psd, n, nd, df, m_lo, m_hi, win_half, tw, D);
+    const int64_t blocks = cols * w.n_blk * w.n_sl;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const size_t lds = (size_t)kWinC * kWinX * 8 + 64 * 16 + (size_t)__builtin_popcount(slabs) * kWinSlab * 16;
+    hipError_t e = hipFuncSetAttribute((const void *)k_qv_win, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_qv_win, dim3((unsigned)blocks), dim3(kWinThreads), lds, st, (const double2 *)hlm, D, tw, n, na,
+                       nd, n_pa, w.n_blk, w.n_sl, w.m1_per, m_lo, m_hi, slabs, n_time,
+                       w.n_sl > 1 ? part : (double2 *)Q);
+    if (w.n_sl > 1) {
+        const int64_t qe = cols * n_time;
+        hipLaunchKernelGGL(k_qv_reduce, dim3((unsigned)std::min<int64_t>((qe + 255) / 256, 65536)), dim3(256), 0, st,
+                           part, w.n_sl, cols, n_time, (double2 *)Q);
+    }
+    launch_uv(hlm, inv_psd, m_lo, n_half, n, na, nd, np, df, (double *)part, (int64_t)u.n_sl * u.per_sl, U, V, st);
     return hipGetLastError();
 }
 

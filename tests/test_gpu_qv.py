@@ -205,6 +205,37 @@ def test_overlaps_decimated_every_radix(orc, n, df, n_time, win_half, radix, til
     _close(Vg[0], Vo)
 
 
+@pytest.mark.parametrize("n,n_time,win_half,npt,na,nd,full", [
+    (512, 512, 256, 1, 2, 1, True),        # one transform per column, every bin (0 and Nyquist on the band)
+    (1024, 1, 0, 2, 3, 2, True),           # two, one window time
+    (1536, 511, 700, 1, 3, 5, False),      # three (a ragged chunk); the window ends before the reference time
+    (2560, 513, -3, 1, 2, 2, False),       # five; two window blocks, the second of one time
+    (3072, 1100, 500, 1, 2, 3, False),     # six (two chunks, the last ragged); three window blocks
+    (16384, 410, 205, 1, 5, 3, False),     # the event grid, one point: a chunk per m1 slice
+])
+def test_overlaps_windowed_fft(orc, n, n_time, win_half, npt, na, nd, full):
+    """The automatic route on grids that are multiples of 512 (interleaved
+    512-point FFTs): edges of the chunks, window blocks and slices, with a PSD
+    weight that differs between f and -f, and NaN mode values off the band
+    (never read), against the oracle."""
+    rng = np.random.default_rng(150 + n + n_time)
+    df = 0.5
+    f = np.abs(np.fft.fftfreq(n, 1.0 / (n * df)))
+    f_lo, f_hi = (0.0, 0.5 * n * df) if full else (5.0 * df, 0.3 * n * df)
+    hl = rng.normal(size=(npt, na, n)) + 1j * rng.normal(size=(npt, na, n))
+    data = rng.normal(size=(nd, n)) + 1j * rng.normal(size=(nd, n))
+    w = rng.uniform(0.5, 1.5, (nd, n))
+    bad = hl.copy()
+    bad[:, :, (f < f_lo) | (f > f_hi)] = np.nan
+    Qg, Ug, Vg = _gpu(bad, data, df, f_lo, f_hi, n_time, win_half, inv_psd=w)
+    for p in range(npt):
+        Qo, Uo, Vo = orc.overlaps_qv(hl[p], data, w, df, f_lo, f_hi, n_time, win_half)
+        up = np.triu(Vo)                       # V is formed for a <= b and mirrored
+        _close(Qg[p], Qo)
+        _close(Ug[p], Uo)
+        _close(Vg[p], up + np.transpose(np.triu(Vo, 1), (0, 2, 1)))
+
+
 def test_overlaps_decimated_refused_without_radix():
     """A prime grid length has no radix: the forced decimated route is an
     error (ILE_E_INVALID), and the automatic route still answers."""
