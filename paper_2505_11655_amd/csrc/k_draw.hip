@@ -470,14 +470,11 @@ hipError_t launch_draw(int policy, const DrawJob *d_jobs, const Tile *d_tiles, i
 // ------------------------------------------------------------------ in-support mass
 // Z_j of each job's mixture: the fraction of z_draws candidates of component j
 // (Philox counter (i, 0x5A000000 + j, round, block)) that fall in the support.
+// The factor kernel that precedes it on the stream has cleared the counters.
 namespace {
 
 constexpr int kZThreads = 256;
 constexpr int kZBlocks = 64;
-
-__global__ void k_gmm_zero(const EmJob *__restrict__ jobs) {
-    if (threadIdx.x < kMaxComp) jobs[blockIdx.z].zcount[threadIdx.x] = 0u;
-}
 
 __global__ void __launch_bounds__(kZThreads) k_gmm_inbox(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
@@ -508,34 +505,44 @@ __global__ void __launch_bounds__(kZThreads) k_gmm_inbox(const EmJob *__restrict
     if (threadIdx.x == 0 && j < g.n_comp) atomicAdd(&J.zcount[j], sacc[0]);
 }
 
+// ln Z_j and the constants of the draw density, one lane per component: r_j =
+// (1 - Z_j)^64, pi_j normalised; the sums over components in their order.
 __global__ void k_gmm_setz(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
     GmmDev *g = J.gmm;
-    const int j = threadIdx.x;
-    if (j < g->n_comp) {
+    const int j = threadIdx.x, nc = g->n_comp;
+    const double wj = j < nc ? g->w[j] : 0.0;
+    double lnz = 0.0;
+    if (j < nc) {
         const double c = (double)J.zcount[j];
-        g->lnZ[j] = log((c > 0 ? c : 0.5) / (double)J.z_draws);
+        lnz = log((c > 0 ? c : 0.5) / (double)J.z_draws);
+        g->lnZ[j] = lnz;
     }
-    __syncthreads();
-    if (j != 0) return;
-    // constants of the draw density: r_j = (1 - Z_j)^64, pi_j normalised
     double tot = 0.0;
-    for (int q = 0; q < g->n_comp; q++) tot += g->w[q] > 0.0 ? g->w[q] : 0.0;
+    for (int q = 0; q < nc; q++) {
+        const double w = __shfl(wj, q, 64);
+        tot += w > 0.0 ? w : 0.0;
+    }
     const double eps = g->eps_def;
-    double fb = eps;
-    for (int q = 0; q < kMaxComp; q++) {
-        if (q >= g->n_comp || !(g->w[q] > 0.0) || !(tot > 0.0)) {
-            g->lnc[q] = -INFINITY;
-            continue;
-        }
-        const double pi = g->w[q] / tot, z = exp(g->lnZ[q]);
+    const bool on = j < nc && wj > 0.0 && tot > 0.0;
+    double term = 0.0;
+    if (on) {
+        const double pi = wj / tot, z = exp(lnz);
         const double lr = (double)kMaxAttempts * log1p(-(z < 1.0 ? z : 1.0));   // ln r_j
-        fb += (1.0 - eps) * pi * exp(lr);
+        term = (1.0 - eps) * pi * exp(lr);
         // ln(1 - r_j), accurate on both sides of r_j = 1/2
         const double l1mr = lr > -0.69314718055994531 ? log(-expm1(lr)) : log1p(-exp(lr));
-        g->lnc[q] = log1p(-eps) + log(pi) + l1mr - g->lnZ[q];
+        g->lnc[j] = log1p(-eps) + log(pi) + l1mr - lnz;
+    } else if (j < kMaxComp) {
+        g->lnc[j] = -INFINITY;
     }
-    g->ln_fb = fb > 0.0 ? log(fb) : -INFINITY;
+    const unsigned long long mask = __ballot(on);
+    double fb = eps;
+    for (int q = 0; q < nc; q++) {
+        const double t = __shfl(term, q, 64);
+        if ((mask >> q) & 1) fb += t;
+    }
+    if (j == 0) g->ln_fb = fb > 0.0 ? log(fb) : -INFINITY;
 }
 
 }  // namespace
@@ -543,7 +550,6 @@ __global__ void k_gmm_setz(const EmJob *__restrict__ jobs) {
 hipError_t launch_gmm_mass(const EmJob *d_jobs, int n_jobs, hipStream_t st) {
     if (n_jobs <= 0) return hipSuccess;
     if (n_jobs > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gmm_zero, dim3(1, 1, n_jobs), dim3(64), 0, st, d_jobs);
     hipLaunchKernelGGL(k_gmm_inbox, dim3(kZBlocks, kMaxComp, n_jobs), dim3(kZThreads), 0, st, d_jobs);
     hipLaunchKernelGGL(k_gmm_setz, dim3(1, 1, n_jobs), dim3(64), 0, st, d_jobs);
     return hipGetLastError();

@@ -16,7 +16,14 @@
 //
 // Every kernel serves a batch of jobs (blockIdx.z = job): the refits of all
 // jobs of a serving pass are one launch per stage.  Per-sample stages tile
-// each job's samples (kEmTile per block); per-job stages are one block each.
+// each job's samples (em_layout: at most 256 tiles, a function of the job's n
+// alone, so that a job's result does not depend on its batch); per-job stages
+// are one block each, with one wave per mixture component.
+// A refit of one job of 2^16 samples is latency: with 8,192 samples per tile
+// it ran on eight CUs (moments 28 us, tempering 102 us against 14), the component
+// update summed and factored in one thread per component (35 us against 10.5),
+// and the responsibilities made a round trip through memory; the whole refit
+// of that size with its installation and draw took 1057 us against 467.
 #include <type_traits>
 
 #include "ile_internal.h"
@@ -29,29 +36,31 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kEmThreads = 256;
-constexpr int kTopThreads = 128;
+constexpr int kEmMaxTiles = 256;
 constexpr int kTopK = 2 * kMaxComp;
-constexpr int64_t kEmTile = 8192;
 constexpr int kBetaGrid = 48;   // beta_k = 2^(-k/4)
-constexpr int kBetaChunk = 8;   // grid values per block reduction
+constexpr int kBetaChunk = 16;   // grid values per block reduction
+constexpr int kMom = 36;        // W, 7 first and 28 second moments
 
-// Work buffer of one job (doubles): scalars, old means, offsets, then the
-// per-tile partials of each stage and the responsibilities.
+// Work buffer of one job (doubles): scalars, then the per-tile partials of
+// each stage.  Tiles of whole blocks of samples, one per CU from 2^16 samples
+// up: the smallest tile that keeps the count at kEmMaxTiles.
 constexpr int kWMax = 0, kWCount = 1, kWBeta = 2, kWPart = 64;
 struct EmLayout {
-    int64_t nblk;
-    size_t stat, init, beta, max, top, R, total;
+    int64_t tile, nblk;
+    size_t stat, init, beta, max, top, total;
 };
 __host__ __device__ inline EmLayout em_layout(int64_t n) {
     EmLayout L;
-    L.nblk = (n + kEmTile - 1) / kEmTile;
+    const int64_t blocks = (n + kEmThreads - 1) / kEmThreads;
+    L.tile = (blocks + kEmMaxTiles - 1) / kEmMaxTiles * kEmThreads;
+    L.nblk = (n + L.tile - 1) / L.tile;
     L.stat = kWPart;
-    L.init = L.stat + (size_t)kMaxComp * L.nblk * 36;
-    L.beta = L.init + (size_t)L.nblk * 36;
+    L.init = L.stat + (size_t)kMaxComp * L.nblk * kMom;
+    L.beta = L.init + (size_t)L.nblk * kMom;
     L.max = L.beta + (size_t)L.nblk * 2 * kBetaGrid;
     L.top = L.max + (size_t)L.nblk * 2;
-    L.R = L.top + (size_t)L.nblk * 2 * kTopK;
-    L.total = L.R + (size_t)kMaxComp * n;
+    L.total = L.top + (size_t)L.nblk * 2 * kTopK;
     return L;
 }
 
@@ -83,40 +92,6 @@ __device__ __forceinline__ double wrapd(double d, double P) {
     return r > 0.5 * P ? r - P : r;
 }
 
-__device__ void factor_one(GmmDev &g, int j) {
-    const int d = g.n_dim;
-    double L[7][7], Li[7][7];
-    for (int a = 0; a < 7; a++)
-        for (int b = 0; b < 7; b++) { L[a][b] = 0.0; Li[a][b] = 0.0; }
-    bool ok = true;
-    for (int c = 0; c < d; c++) {
-        double s = g.cov[j][c][c];
-        for (int k = 0; k < c; k++) s -= L[c][k] * L[c][k];
-        if (!(s > 0.0)) { ok = false; s = 1e-300; }
-        L[c][c] = sqrt(s);
-        for (int r = c + 1; r < d; r++) {
-            double t = g.cov[j][r][c];
-            for (int k = 0; k < c; k++) t -= L[r][k] * L[c][k];
-            L[r][c] = t / L[c][c];
-        }
-    }
-    // inverse of the lower factor, column by column (forward substitution)
-    for (int c = 0; c < d; c++) {
-        for (int r = 0; r < d; r++) {
-            double t = (r == c) ? 1.0 : 0.0;
-            for (int k = 0; k < r; k++) t -= L[r][k] * Li[k][c];
-            Li[r][c] = (r < c) ? 0.0 : t / L[r][r];
-        }
-    }
-    double ld = 0.0;
-    for (int c = 0; c < d; c++) ld += log(L[c][c]);
-    for (int a = 0; a < 7; a++)
-        for (int b = 0; b < 7; b++) { g.L[j][a][b] = L[a][b]; g.Linv[j][a][b] = Li[a][b]; }
-    g.logdet_half[j] = ld;
-    g.logw[j] = (g.w[j] > 0.0) ? log(g.w[j]) : -INFINITY;
-    if (!ok) g.valid = 0;
-}
-
 template <class TT>
 __device__ __forceinline__ double load_col(const TT *th, int64_t ld, int col, int64_t i) {
     return (double)th[col * ld + i];
@@ -136,31 +111,162 @@ __device__ __forceinline__ double sample_weight(double lwv, double mlw, double b
     return finite_d(lwv) ? exp(beta * (lwv - mlw)) : 0.0;
 }
 
-// Block sum of NV doubles per thread into out[0..NV): a butterfly within
-// each wave (lane 0's association order is fixed), then the waves in order.
+// Sums of NV values over the group of 2 OFF consecutive lanes that a lane
+// belongs to, each lane keeping part of them: at every step the lanes of a
+// pair split what is left (half the values travel, where a butterfly over
+// every value moves them all at each step).  Afterwards v[0 .. lim) of a lane
+// are the sums of values base .. base + lim - 1 (association fixed by the lane
+// numbers; lanes that share a value hold the same sum).
+template <int NV, int OFF>
+__device__ __forceinline__ void lane_sums(double *v, int lane, int &base, int &lim) {
+    if constexpr (OFF > 0) {
+        if constexpr (NV == 1) {
+            v[0] += __shfl_xor(v[0], OFF, 64);
+            lane_sums<1, OFF / 2>(v, lane, base, lim);
+        } else {
+            constexpr int H = (NV + 1) / 2;
+            const bool up = (lane & OFF) != 0;
+#pragma unroll
+            for (int i = 0; i < H; i++) {
+                const double lo = v[i], hi = i + H < NV ? v[i + H] : 0.0;
+                v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, OFF, 64);
+            }
+            base += up ? H : 0;
+            lim = up ? lim - H : (lim < H ? lim : H);
+            lane_sums<H, OFF / 2>(v, lane, base, lim);
+        }
+    }
+}
 template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double *out) {
+constexpr int lane_left(int off) {
+    int n = NV;
+    for (; off > 0; off /= 2) n = (n + 1) / 2;
+    return n;
+}
+
+// Block sum of NV doubles per thread into out[0], out[stride], ..: within each
+// wave (lane_sums), then the waves in order.
+template <int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV], double *out, int64_t stride) {
     __shared__ double red[kEmThreads / 64][NV];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int base = 0, lim = NV;
+    lane_sums<NV, 32>(v, lane, base, lim);
 #pragma unroll
-    for (int c = 0; c < NV; c++) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_xor(v[c], off, 64);
-    }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-        for (int c = 0; c < NV; c++) red[w][c] = v[c];
-    }
+    for (int t = 0; t < lane_left<NV>(32); t++)
+        if (t < lim) red[w][base + t] = v[t];
     __syncthreads();
     for (int c = threadIdx.x; c < NV; c += blockDim.x) {
         double s = red[0][c];
         for (int q = 1; q < kEmThreads / 64; q++) s += red[q][c];
-        out[c] = s;
+        out[c * stride] = s;
     }
     __syncthreads();
 }
 
+// Cholesky factor L of component j's covariance, L^{-1}, sum ln diag(L) and
+// ln pi_j by one wave: lane r < d holds row r of the covariance (lower part)
+// and of L; then lane c holds column c of the inverse.
+__device__ void wave_factor(GmmDev &g, int j, int lane, int d, const double (&cov)[7]) {
+    double L[7], Li[7];
+    bool ok = true;
+#pragma unroll
+    for (int c = 0; c < 7; c++) L[c] = 0.0;
+#pragma unroll
+    for (int c = 0; c < 7; c++) {
+        if (c >= d) break;
+        // every lane r >= c: t = cov[r][c] - sum_k L[r][k] L[c][k]
+        double t = cov[c];
+#pragma unroll
+        for (int k = 0; k < c; k++) t -= L[k] * __shfl(L[k], c, 64);
+        double s = __shfl(t, c, 64);
+        if (!(s > 0.0)) {
+            ok = false;
+            s = 1e-300;
+        }
+        const double dg = sqrt(s);
+        L[c] = lane == c ? dg : (lane > c && lane < d ? t / dg : 0.0);
+    }
+#pragma unroll
+    for (int r = 0; r < 7; r++) {
+        if (r >= d) {
+            Li[r] = 0.0;
+            continue;
+        }
+        double t = (r == lane) ? 1.0 : 0.0;
+#pragma unroll
+        for (int k = 0; k < r; k++) t -= __shfl(L[k], r, 64) * Li[k];
+        const double dg = __shfl(L[r], r, 64);
+        Li[r] = (r < lane || lane >= d) ? 0.0 : t / dg;
+    }
+    double own = 1.0;
+#pragma unroll
+    for (int c = 0; c < 7; c++) own = (c == lane && c < d) ? L[c] : own;
+    const double lg = log(own);
+    double ld = 0.0;
+    for (int c = 0; c < d; c++) ld += __shfl(lg, c, 64);
+    if (lane < 7) {
+#pragma unroll
+        for (int b = 0; b < 7; b++) {
+            g.L[j][lane][b] = lane < d ? L[b] : 0.0;
+            g.Linv[j][b][lane] = Li[b];
+        }
+    }
+    if (lane == 0) {
+        g.logdet_half[j] = ld;
+        g.logw[j] = (g.w[j] > 0.0) ? log(g.w[j]) : -INFINITY;
+        if (!ok) g.valid = 0;
+    }
+}
+
+// Sums over the tiles of NV consecutive values of a [value][tile] partial array
+// by one wave: a lane takes every 64th tile (every load in flight at once),
+// then lane_sums.  Into out[0 .. NV) (LDS).
+template <int NV>
+__device__ __forceinline__ void tile_sums(const double *p, int64_t nblk, int lane, double *out) {
+    static_assert(kEmMaxTiles <= 256, "four tiles per lane");
+    double v[NV];
+#pragma unroll
+    for (int c = 0; c < NV; c++) {
+        double t[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) t[q] = lane + 64 * q < nblk ? p[c * nblk + lane + 64 * q] : 0.0;
+        v[c] = (t[0] + t[1]) + (t[2] + t[3]);
+    }
+    int base = 0, lim = NV;
+    lane_sums<NV, 32>(v, lane, base, lim);
+#pragma unroll
+    for (int t = 0; t < lane_left<NV>(32); t++)
+        if (t < lim) out[base + t] = v[t];
+}
+// A component's 36 moments, twelve at a time (96 registers in flight).
+__device__ __forceinline__ void moment_sums(const double *p, int64_t nblk, int lane, double *out) {
+#pragma unroll 1
+    for (int c = 0; c < kMom; c += 12) tile_sums<12>(p + (size_t)c * nblk, nblk, lane, out + c);
+}
+
 // ------------------------------------------------------------- weights
+// Block maximum and sum of one pair per thread (every thread gets them).
+__device__ __forceinline__ void block_max_sum(double &m, double &c) {
+    __shared__ double sm[kEmThreads / 64], sc[kEmThreads / 64];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        m = fmax(m, __shfl_xor(m, off, 64));
+        c += __shfl_xor(c, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sm[threadIdx.x >> 6] = m;
+        sc[threadIdx.x >> 6] = c;
+    }
+    __syncthreads();
+    m = sm[0];
+    c = sc[0];
+    for (int w = 1; w < kEmThreads / 64; w++) {
+        m = fmax(m, sm[w]);
+        c += sc[w];
+    }
+}
+
 // per tile: max of the finite lw and their count
 template <class TL>
 __global__ void __launch_bounds__(kEmThreads) k_em_scan(const EmJob *__restrict__ jobs) {
@@ -168,7 +274,7 @@ __global__ void __launch_bounds__(kEmThreads) k_em_scan(const EmJob *__restrict_
     const EmLayout Lo = em_layout(J.n);
     if (blockIdx.x >= Lo.nblk) return;
     const TL *__restrict__ lw = (const TL *)J.lw;
-    const int64_t b0 = (int64_t)blockIdx.x * kEmTile, b1 = min(b0 + kEmTile, J.n);
+    const int64_t b0 = (int64_t)blockIdx.x * Lo.tile, b1 = min(b0 + Lo.tile, J.n);
     double m = -INFINITY, c = 0.0;
     for (int64_t i = b0 + threadIdx.x; i < b1; i += kEmThreads) {
         const double v = (double)lw[i];
@@ -177,94 +283,77 @@ __global__ void __launch_bounds__(kEmThreads) k_em_scan(const EmJob *__restrict_
             c += 1.0;
         }
     }
-    __shared__ double sm[kEmThreads], sc[kEmThreads];
-    sm[threadIdx.x] = m;
-    sc[threadIdx.x] = c;
-    __syncthreads();
-    for (int w = kEmThreads / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            sm[threadIdx.x] = fmax(sm[threadIdx.x], sm[threadIdx.x + w]);
-            sc[threadIdx.x] += sc[threadIdx.x + w];
-        }
-        __syncthreads();
-    }
+    block_max_sum(m, c);
     if (threadIdx.x == 0) {
-        J.work[Lo.max + 2 * blockIdx.x] = sm[0];
-        J.work[Lo.max + 2 * blockIdx.x + 1] = sc[0];
+        J.work[Lo.max + 2 * blockIdx.x] = m;
+        J.work[Lo.max + 2 * blockIdx.x + 1] = c;
     }
 }
 
-__global__ void k_em_scan_final(const EmJob *__restrict__ jobs) {
-    const EmJob &J = jobs[blockIdx.z];
-    if (threadIdx.x != 0) return;
-    const EmLayout Lo = em_layout(J.n);
-    double m = -INFINITY, c = 0.0;
-    for (int64_t b = 0; b < Lo.nblk; b++) {
-        m = fmax(m, J.work[Lo.max + 2 * b]);
-        c += J.work[Lo.max + 2 * b + 1];
-    }
-    J.work[kWMax] = m;
-    J.work[kWCount] = c;
-    J.work[kWBeta] = 1.0;
-}
-
-// Tempering exponent: the largest beta_k = 2^(-k/4) whose tempered weights
-// have (sum w^beta)^2 / sum w^(2 beta) >= frac * (finite samples).  Per tile:
-// the 48 pairs (sum w^beta_k, sum w^(2 beta_k)).
+// Every block reduces the tiles' maxima and counts (the first one stores
+// them).  Tempering exponent: the largest beta_k = 2^(-k/4) whose tempered
+// weights have (sum w^beta)^2 / sum w^(2 beta) >= frac * (finite samples).
+// Per tile: the 48 pairs (sum w^beta_k, sum w^(2 beta_k)).
 template <class TL>
 __global__ void __launch_bounds__(kEmThreads) k_em_beta(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
     const EmLayout Lo = em_layout(J.n);
-    if (blockIdx.x >= Lo.nblk || !(J.temper > 0.0)) return;
-    const TL *__restrict__ lw = (const TL *)J.lw;
-    const double mlw = J.work[kWMax];
-    constexpr int kPer = (int)(kEmTile / kEmThreads);
-    const int64_t b0 = (int64_t)blockIdx.x * kEmTile;
-    double x[kPer];
-#pragma unroll
-    for (int s = 0; s < kPer; s++) {
-        const int64_t i = b0 + threadIdx.x + (int64_t)s * kEmThreads;
-        const double v = i < J.n ? (double)lw[i] : -INFINITY;
-        x[s] = finite_d(v) ? v - mlw : -INFINITY;
+    const bool temper = J.temper > 0.0;
+    if (blockIdx.x >= Lo.nblk || (!temper && blockIdx.x > 0)) return;
+    static_assert(kEmMaxTiles <= kEmThreads, "one tile's maximum per thread");
+    double mlw = -INFINITY, cnt = 0.0;
+    if (threadIdx.x < Lo.nblk) {
+        mlw = J.work[Lo.max + 2 * threadIdx.x];
+        cnt = J.work[Lo.max + 2 * threadIdx.x + 1];
     }
-    double *out = J.work + Lo.beta + (size_t)blockIdx.x * 2 * kBetaGrid;
+    block_max_sum(mlw, cnt);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        J.work[kWMax] = mlw;
+        J.work[kWCount] = cnt;
+        J.work[kWBeta] = 1.0;
+    }
+    if (!temper) return;
+    const TL *__restrict__ lw = (const TL *)J.lw;
+    const int64_t b0 = (int64_t)blockIdx.x * Lo.tile, b1 = min(b0 + Lo.tile, J.n);
+    double *out = J.work + Lo.beta + blockIdx.x;
     for (int c0 = 0; c0 < kBetaGrid; c0 += kBetaChunk) {
-        double acc[2 * kBetaChunk];
+        double acc[2 * kBetaChunk], bk[kBetaChunk];
 #pragma unroll
         for (int q = 0; q < kBetaChunk; q++) {
-            const double b = exp2(-(double)(c0 + q) / 4.0);
-            double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-            for (int s = 0; s < kPer; s++) {
-                const double e = exp(b * x[s]);
-                s1 += e;
-                s2 += e * e;
-            }
-            acc[2 * q] = s1;
-            acc[2 * q + 1] = s2;
+            bk[q] = exp2(-(double)(c0 + q) / 4.0);
+            acc[2 * q] = 0.0;
+            acc[2 * q + 1] = 0.0;
         }
-        block_sum<2 * kBetaChunk>(acc, out + 2 * c0);
+        for (int64_t i = b0 + threadIdx.x; i < b1; i += kEmThreads) {
+            const double v = (double)lw[i];
+            const double x = finite_d(v) ? v - mlw : -INFINITY;
+#pragma unroll
+            for (int q = 0; q < kBetaChunk; q++) {
+                const double e = exp(bk[q] * x);
+                acc[2 * q] += e;
+                acc[2 * q + 1] += e * e;
+            }
+        }
+        block_sum<2 * kBetaChunk>(acc, out + (size_t)2 * c0 * Lo.nblk, Lo.nblk);
     }
 }
 
-__global__ void k_em_beta_final(const EmJob *__restrict__ jobs) {
+__global__ void __launch_bounds__(256) k_em_beta_final(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
-    if (threadIdx.x != 0 || !(J.temper > 0.0)) return;
+    if (!(J.temper > 0.0)) return;
     const EmLayout Lo = em_layout(J.n);
+    __shared__ double s[2 * kBetaGrid];
+    constexpr int kPer = 2 * kBetaGrid / 4;   // values per wave
+    const int wv = threadIdx.x >> 6;
+    tile_sums<kPer>(J.work + Lo.beta + (size_t)wv * kPer * Lo.nblk, Lo.nblk, threadIdx.x & 63, s + wv * kPer);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
     const double target = J.temper * J.work[kWCount];
-    double beta = exp2(-(double)(kBetaGrid - 1) / 4.0);
-    for (int k = 0; k < kBetaGrid; k++) {
-        double s1 = 0.0, s2 = 0.0;
-        for (int64_t b = 0; b < Lo.nblk; b++) {
-            s1 += J.work[Lo.beta + (size_t)b * 2 * kBetaGrid + 2 * k];
-            s2 += J.work[Lo.beta + (size_t)b * 2 * kBetaGrid + 2 * k + 1];
-        }
-        if (s1 * s1 / s2 >= target) {
-            beta = exp2(-(double)k / 4.0);
-            break;
-        }
-    }
-    J.work[kWBeta] = beta;
+    const int k = threadIdx.x < kBetaGrid ? threadIdx.x : kBetaGrid - 1;
+    const double s1 = s[2 * k], s2 = s[2 * k + 1];
+    const unsigned long long hit = __ballot(s1 * s1 / s2 >= target) & ((1ull << kBetaGrid) - 1);
+    const int first = hit ? __ffsll((long long)hit) - 1 : kBetaGrid - 1;
+    if (threadIdx.x == 0) J.work[kWBeta] = exp2(-(double)first / 4.0);
 }
 
 // ---------------------------------------------------------------- first fit
@@ -275,52 +364,58 @@ struct Cand {
 __device__ __forceinline__ bool better(const Cand &a, const Cand &b) {
     return a.v > b.v || (a.v == b.v && a.i < b.i);
 }
-__device__ __forceinline__ void merge_top(const Cand *A, const Cand *B, Cand *out) {
-    int ia = 0, ib = 0;
-    for (int k = 0; k < kTopK; k++) out[k] = better(B[ib], A[ia]) ? B[ib++] : A[ia++];
+// The block's best candidate (every thread gets it).
+__device__ __forceinline__ Cand block_best(Cand c, Cand *sh) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const Cand o{__shfl_xor(c.v, off, 64), (int64_t)__shfl_xor((long long)c.i, off, 64)};
+        c = better(o, c) ? o : c;
+    }
+    __syncthreads();   // the previous round's reads are done
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
+    __syncthreads();
+    c = sh[0];
+    for (int w = 1; w < kEmThreads / 64; w++) c = better(sh[w], c) ? sh[w] : c;
+    return c;
 }
+// candidates of a first fit: the 2 n_comp highest-weight samples
+__device__ __forceinline__ int top_count(const EmJob &J) { return 2 * J.n_comp < kTopK ? 2 * J.n_comp : kTopK; }
 
-// per tile: the kTopK highest finite lw (ties: lower index first)
+// per tile: the highest finite lw (ties: lower index first), one round per
+// candidate: the best sample that comes after the previous round's
 template <class TL>
-__global__ void __launch_bounds__(kTopThreads) k_em_top(const EmJob *__restrict__ jobs) {
+__global__ void __launch_bounds__(kEmThreads) k_em_top(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
     const EmLayout Lo = em_layout(J.n);
     if (!J.first || blockIdx.x >= Lo.nblk) return;
     const TL *__restrict__ lw = (const TL *)J.lw;
-    __shared__ Cand lists[kTopThreads][kTopK];
-    Cand loc[kTopK];
-    for (int k = 0; k < kTopK; k++) loc[k] = Cand{-INFINITY, INT64_MAX};
-    const int64_t b0 = (int64_t)blockIdx.x * kEmTile, b1 = min(b0 + kEmTile, J.n);
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += kTopThreads) {
-        const double v = (double)lw[i];
-        if (!finite_d(v)) continue;
-        Cand c{v, i};
-        if (!better(c, loc[kTopK - 1])) continue;
-        int k = kTopK - 1;
-        while (k > 0 && better(c, loc[k - 1])) { loc[k] = loc[k - 1]; k--; }
-        loc[k] = c;
-    }
-    for (int k = 0; k < kTopK; k++) lists[threadIdx.x][k] = loc[k];
-    __syncthreads();
-    for (int w = kTopThreads / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            Cand out[kTopK];
-            merge_top(lists[threadIdx.x], lists[threadIdx.x + w], out);
-            for (int k = 0; k < kTopK; k++) lists[threadIdx.x][k] = out[k];
+    __shared__ Cand sh[kEmThreads / 64];
+    const int64_t b0 = (int64_t)blockIdx.x * Lo.tile, b1 = min(b0 + Lo.tile, J.n);
+    double *o = J.work + Lo.top + (size_t)blockIdx.x * 2 * kTopK;
+    const int nk = top_count(J);
+    Cand prev{INFINITY, -1};
+    for (int k = 0; k < nk; k++) {
+        Cand best{-INFINITY, INT64_MAX};
+        if (prev.v > -INFINITY) {
+            for (int64_t i = b0 + threadIdx.x; i < b1; i += kEmThreads) {
+                const Cand c{(double)lw[i], i};
+                if (finite_d(c.v) && better(prev, c) && better(c, best)) best = c;
+            }
+            best = block_best(best, sh);
         }
-        __syncthreads();
-    }
-    if (threadIdx.x < kTopK) {
-        double *o = J.work + Lo.top + (size_t)blockIdx.x * 2 * kTopK;
-        o[2 * threadIdx.x] = lists[0][threadIdx.x].v;
-        o[2 * threadIdx.x + 1] = (double)lists[0][threadIdx.x].i;
+        if (threadIdx.x == 0) {
+            o[2 * k] = best.v;
+            o[2 * k + 1] = (double)best.i;
+        }
+        prev = best;
     }
 }
 
-// merge the tiles' lists; reset the mixture and place the means at the
-// highest-weight distinct samples
+// merge the tiles' sorted lists (one per thread, its head advanced when it
+// wins a round); reset the mixture and place the means at the highest-weight
+// distinct samples
 template <class TT>
-__global__ void k_em_top_final(const EmJob *__restrict__ jobs) {
+__global__ void __launch_bounds__(kEmThreads) k_em_top_final(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
     if (!J.first) return;
     GmmDev *g = J.gmm;
@@ -329,53 +424,56 @@ __global__ void k_em_top_final(const EmJob *__restrict__ jobs) {
         const size_t nd = sizeof(GmmDev) / sizeof(double);
         for (size_t k = threadIdx.x; k < nd; k += blockDim.x) p[k] = 0.0;
     }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
     const EmLayout Lo = em_layout(J.n);
-    Cand cur[kTopK], nxt[kTopK], add[kTopK];
-    for (int k = 0; k < kTopK; k++) cur[k] = Cand{-INFINITY, INT64_MAX};
-    for (int64_t b = 0; b < Lo.nblk; b++) {
-        const double *o = J.work + Lo.top + (size_t)b * 2 * kTopK;
-        for (int k = 0; k < kTopK; k++) add[k] = Cand{o[2 * k], (int64_t)o[2 * k + 1]};
-        merge_top(cur, add, nxt);
-        for (int k = 0; k < kTopK; k++) cur[k] = nxt[k];
-    }
-    g->n_dim = J.n_dim;
-    for (int a = 0; a < 7; a++) g->dims[a] = a < J.n_dim ? J.dims[a] : 0;
-    g->eps_def = J.eps_def;
-    g->valid = 1;
     const TT *th = (const TT *)J.theta;
-    const int d = J.n_dim, nc = J.n_comp;
+    const int d = J.n_dim, nc = J.n_comp, nk = top_count(J);
+    __shared__ Cand sh[kEmThreads / 64], cur[kTopK];
+    __shared__ double sx[kTopK][7];
+    const double *o = J.work + Lo.top + (size_t)threadIdx.x * 2 * kTopK;
+    int pos = 0;
+    for (int k = 0; k < nk; k++) {
+        Cand c{-INFINITY, INT64_MAX};
+        if (threadIdx.x < Lo.nblk && pos < nk && o[2 * pos] > -INFINITY) c = Cand{o[2 * pos], (int64_t)o[2 * pos + 1]};
+        const Cand b = block_best(c, sh);
+        if (b.v > -INFINITY && b.i == c.i) pos++;
+        if (threadIdx.x == 0) cur[k] = b;
+    }
+    __syncthreads();
     // phase shear from the inclination of the best sample: face-on
     // (cos iota >= 1/2, where the m = +2 end of each multiplet dominates) the
     // ridge runs along psi + phi_c, face-off along psi - phi_c; in between
     // there is no single ridge and the phases stay as they are
-    g->shear = 0;
+    int shear = 0;
     if (J.shear_auto && cur[0].v > -INFINITY) {
         const double ci = load_col(th, J.ld, 4, cur[0].i);
-        g->shear = ci >= 0.5 ? 1 : (ci <= -0.5 ? -1 : 0);
+        shear = ci >= 0.5 ? 1 : (ci <= -0.5 ? -1 : 0);
     }
-    // candidates: the 2 n_comp highest-weight samples (kTopK = 2 kMaxComp
-    // holds them for every n_comp), scanned in that order
-    const int ncand = 2 * nc < kTopK ? 2 * nc : kTopK;
-    int got = 0;
-    for (int k = 0; k < ncand && got < nc; k++) {
+    if ((int)threadIdx.x < 8 * nk) {
+        const int k = threadIdx.x >> 3, a = threadIdx.x & 7;
+        if (a < d && cur[k].v > -INFINITY) sx[k][a] = load_mix(th, J.ld, J.dims[a], cur[k].i, shear);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    g->n_dim = d;
+    for (int a = 0; a < 7; a++) g->dims[a] = a < d ? J.dims[a] : 0;
+    g->eps_def = J.eps_def;
+    g->valid = 1;
+    g->shear = shear;
+    // the distinct candidates in their order
+    int got = 0, from[kMaxComp];
+    for (int k = 0; k < nk && got < nc; k++) {
         if (!(cur[k].v > -INFINITY)) break;
-        double x[7];
-        for (int a = 0; a < d; a++) x[a] = load_mix(th, J.ld, J.dims[a], cur[k].i, g->shear);
         bool dup = false;
         for (int q = 0; q < got && !dup; q++) {
             bool same = true;
-            for (int a = 0; a < d; a++) same = same && (x[a] == g->mean[q][a]);
+            for (int a = 0; a < d; a++) same = same && (sx[k][a] == sx[from[q]][a]);
             dup = same;
         }
-        if (dup) continue;
-        for (int a = 0; a < d; a++) g->mean[got][a] = x[a];
-        got++;
+        if (!dup) from[got++] = k;
     }
-    if (got == 0) got = 1;  // no finite weight: keep the first mean as is
-    for (int q = got; q < nc; q++)
-        for (int a = 0; a < d; a++) g->mean[q][a] = g->mean[got - 1][a];
+    // no finite weight: the first mean stays as it is
+    for (int q = 0; q < nc && got > 0; q++)
+        for (int a = 0; a < d; a++) g->mean[q][a] = sx[from[q < got ? q : got - 1]][a];
     g->n_comp = nc;
 }
 
@@ -390,9 +488,9 @@ __global__ void __launch_bounds__(kEmThreads) k_em_init(const EmJob *__restrict_
     const GmmDev *g = J.gmm;
     const int d = g->n_dim;
     const double mlw = J.work[kWMax], beta = J.work[kWBeta];
-    double acc[36];
-    for (int c = 0; c < 36; c++) acc[c] = 0.0;
-    const int64_t b0 = (int64_t)blockIdx.x * kEmTile, b1 = min(b0 + kEmTile, J.n);
+    double acc[kMom];
+    for (int c = 0; c < kMom; c++) acc[c] = 0.0;
+    const int64_t b0 = (int64_t)blockIdx.x * Lo.tile, b1 = min(b0 + Lo.tile, J.n);
     for (int64_t i = b0 + threadIdx.x; i < b1; i += kEmThreads) {
         const double w = sample_weight((double)lw[i], mlw, beta);
         double x[7];
@@ -413,285 +511,307 @@ __global__ void __launch_bounds__(kEmThreads) k_em_init(const EmJob *__restrict_
 #pragma unroll
             for (int b = 0; b <= a; b++) acc[k++] += w * x[a] * x[b];
     }
-    block_sum<36>(acc, J.work + Lo.init + (size_t)blockIdx.x * 36);
+    block_sum<kMom>(acc, J.work + Lo.init + blockIdx.x, Lo.nblk);
 }
 
-__global__ void k_em_init_final(const EmJob *__restrict__ jobs) {
+// Component index of moment 8 + lane (second moments, row by row), lane < 28.
+__device__ __forceinline__ void mom_ab(int t, int &a, int &b) {
+    a = 0;
+    while ((a + 1) * (a + 2) / 2 <= t) a++;
+    b = t - a * (a + 1) / 2;
+}
+
+// One wave per component: covariance rows from the moments s[36] (LDS),
+// centred on the mean offsets, plus the floor; the lane's row (lane < d).
+__device__ __forceinline__ void wave_cov(const double *s, const PriorDev &pr, const GmmDev &g, int lane, int d,
+                                         double (&row)[7], double &m) {
+    const double W = s[0];
+    m = lane < d ? s[1 + lane] / W : 0.0;
+    const int r = lane < 7 ? lane : 0;
+#pragma unroll
+    for (int b = 0; b < 7; b++) {
+        const double mb = __shfl(m, b, 64);
+        const int hi = r > b ? r : b, lo = r > b ? b : r;
+        double v = (lane < d && b < d) ? s[8 + hi * (hi + 1) / 2 + lo] / W - (r >= b ? m * mb : mb * m) : 0.0;
+        if (b == lane && lane < d) {
+            const double rg = col_range(pr, g.dims[lane]);
+            v += 1e-8 * rg * rg;
+        }
+        row[b] = v;
+    }
+}
+
+// The common first covariance, in every component, and its factors.
+__global__ void __launch_bounds__(64 * kMaxComp) k_em_init_final(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
-    if (!J.first || threadIdx.x != 0) return;
+    if (!J.first) return;
     const EmLayout Lo = em_layout(J.n);
     GmmDev *g = J.gmm;
-    double s[36];
-    for (int c = 0; c < 36; c++) s[c] = 0.0;
-    for (int64_t b = 0; b < Lo.nblk; b++)
-        for (int c = 0; c < 36; c++) s[c] += J.work[Lo.init + (size_t)b * 36 + c];
+    const int lane = threadIdx.x & 63, j = threadIdx.x >> 6;
+    __shared__ double s[kMom];
+    if (j == 0) moment_sums(J.work + Lo.init, Lo.nblk, lane, s);
+    __syncthreads();
     const int d = g->n_dim;
-    double mu[7];
-    for (int a = 0; a < 7; a++) mu[a] = (a < d) ? s[1 + a] / s[0] : 0.0;
-    double cov[7][7];
-    int k = 8;
-    for (int a = 0; a < 7; a++)
-        for (int b = 0; b <= a; b++) {
-            const double v = s[k++] / s[0] - mu[a] * mu[b];
-            cov[a][b] = v;
-            cov[b][a] = v;
-        }
-    for (int a = 0; a < d; a++) {
-        const double r = col_range(J.pr, g->dims[a]);
-        cov[a][a] += 1e-8 * r * r;
-    }
-    for (int j = 0; j < g->n_comp; j++) {
-        g->w[j] = 1.0 / g->n_comp;
-        for (int a = 0; a < 7; a++)
-            for (int b = 0; b < 7; b++) g->cov[j][a][b] = (a < d && b < d) ? cov[a][b] : 0.0;
-    }
+    if (j >= g->n_comp) return;
+    double row[7], m;
+    wave_cov(s, J.pr, *g, lane, d, row, m);
+    if (lane < 7)
+        for (int b = 0; b < 7; b++) g->cov[j][lane][b] = row[b];
+    if (lane == 0) g->w[j] = 1.0 / g->n_comp;
+    __threadfence_block();
+    wave_factor(*g, j, lane, d, row);
 }
 
-// only_first: factor just the jobs that had a first fit
-__global__ void k_gmm_factor(const EmJob *__restrict__ jobs, int only_first) {
+__global__ void __launch_bounds__(64 * kMaxComp) k_gmm_factor(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
-    if (only_first && !J.first) return;
     GmmDev *g = J.gmm;
-    const int j = threadIdx.x;
-    if (j == 0) g->valid = 1;
+    const int lane = threadIdx.x & 63, j = threadIdx.x >> 6;
+    if (threadIdx.x == 0) g->valid = 1;
+    if (threadIdx.x < kMaxComp) J.zcount[threadIdx.x] = 0u;   // for the mass estimate that follows
     __syncthreads();
-    if (j < g->n_comp) factor_one(*g, j);
+    if (j >= g->n_comp) return;
+    double row[7];
+#pragma unroll
+    for (int b = 0; b < 7; b++) row[b] = lane < 7 ? g->cov[j][lane][b] : 0.0;
+    wave_factor(*g, j, lane, g->n_dim, row);
 }
 
 // ------------------------------------------------------------------ EM
-// Responsibilities times weights, R_ij = w_i pi_j N_j(x_i) / sum_k pi_k N_k(x_i).
-// The block stages its job's mixture (means, packed inverse factors and the
-// constant ln pi_j - ln det^(1/2) - d/2 ln 2pi) in LDS.
-// The EM kernels take the mixture's dimension count D as a compile-time
-// constant for the common counts (six with the distance integrated, seven
-// otherwise; D = 0: the count read at run time), which removes the
-// per-dimension tests from their unrolled loops.  A kernel compiled for D
-// checks the mixture's count and runs the general body for any other.
-template <class TT, class TL, int D>
-__device__ __forceinline__ void em_resp_body(const EmJob &J, double (&s_mean)[kMaxComp][7],
-                                             double (&s_li)[kMaxComp][28], double (&s_c)[kMaxComp],
-                                             double (&s_lr)[kMaxComp][kEmThreads]) {
-    const EmLayout Lo = em_layout(J.n);
+// E step and the tile's moments in one pass.  A block takes its tile 256
+// samples at a time; they sit in LDS, and 256 / NC consecutive threads serve
+// one component (NC: the component count rounded up to 4, 8 or 16):
+//   ln pi_j N_j(x_i) of its samples, the component's mean and inverse factor in
+//     registers;
+//   then one thread per sample turns the column of LDS into responsibilities
+//     times weights, R_ij = w_i pi_j N_j(x_i) / sum_k pi_k N_k(x_i);
+//   then W_j and the first and second moments of the offsets wrap(x - mu_j),
+//     36 sums per thread (the covariance centred on the mean offset m_j is
+//     S2/W - m_j m_j^T, the same quantity as the centred two-pass sum).
+// The responsibilities never leave the CU.  Latency and FP64 issue bound it:
+// 2^16 samples, 8 components, 6 dimensions: 11.7 us, where responsibilities
+// through memory and moments of 8,192-sample tiles took 13.8 + 28.4 us.
+// The kernel takes the mixture's columns as compile-time constants for the two
+// default sets (D = 6: all but the distance, D = 7: all; D = 0: read at run
+// time), which removes the per-dimension tests and the periods' registers from
+// the unrolled loops; compiled for D it checks the mixture's columns and runs
+// the general body for any others.
+constexpr int mix_col(int D, int a) { return D == 6 && a >= 3 ? a + 1 : a; }
+constexpr double mix_period(int D, int a) {
+    const int c = mix_col(D, a);
+    return (c == 0 || c == 5) ? 2 * kPi : (c == 6 ? kPi : 0.0);
+}
+// wrapd by rounding to the nearest period (the same value but for the last
+// bit, and at exactly half a period, where both images are equally far)
+__device__ __forceinline__ double wrapn(double d, double P, double iP) { return d - P * rint(d * iP); }
+
+struct EmShared {
+    double x[7][kEmThreads];
+    double w[kEmThreads];
+    double r[kMaxComp][kEmThreads];
+};
+
+template <class TT, class TL, int D, int NC>
+__device__ __forceinline__ void em_pass(const EmJob &J, const EmLayout &Lo, EmShared &S) {
+    constexpr int LP = kEmThreads / NC;              // threads per component
+    static_assert(LP <= 64 && NC <= kMaxComp, "whole components per wave");
     const TT *__restrict__ th = (const TT *)J.theta;
     const TL *__restrict__ lw = (const TL *)J.lw;
     const GmmDev *g = J.gmm;
-    double *R = J.work + Lo.R;
-    const int64_t n = J.n;
     const int d = D > 0 ? D : g->n_dim, nc = g->n_comp;
-    for (int t = threadIdx.x; t < kMaxComp * 28; t += kEmThreads) {
-        const int j = t / 28, k = t % 28;
-        int a = 0;
-        while ((a + 1) * (a + 2) / 2 <= k) a++;
-        const int b = k - a * (a + 1) / 2;
-        s_li[j][k] = j < nc ? g->Linv[j][a][b] : 0.0;
-        if (k < 7) s_mean[j][k] = j < nc ? g->mean[j][k] : 0.0;
-        if (k == 0)
-            s_c[j] = (j < nc && g->logw[j] != -INFINITY)
-                         ? g->logw[j] - g->logdet_half[j] - 0.5 * d * log(2 * kPi)
-                         : -INFINITY;
-    }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63, j = tid / LP, l = tid % LP;
+    const bool comp = j < nc;
     int col[7];
-    double P[7];
+    double P[7], iP[7], mu[7], li[28];
 #pragma unroll
     for (int a = 0; a < 7; a++) {
-        col[a] = a < d ? g->dims[a] : 0;
-        P[a] = col_period(col[a]);
+        col[a] = D > 0 ? mix_col(D, a < D ? a : 0) : (a < d ? g->dims[a] : 0);
+        P[a] = D > 0 ? mix_period(D, a) : (a < d ? col_period(col[a]) : 0.0);
+        iP[a] = P[a] > 0.0 ? 1.0 / P[a] : 0.0;
+        mu[a] = comp && a < d ? g->mean[j][a] : 0.0;
+#pragma unroll
+        for (int b = 0; b <= a; b++) li[a * (a + 1) / 2 + b] = comp && a < d ? g->Linv[j][a][b] : 0.0;
     }
+    auto off = [&](int a, double v) {   // wrapped offset from the component's mean
+        const double u = v - mu[a];
+        return (D > 0 && mix_period(D, a) == 0.0) ? u : wrapn(u, P[a], iP[a]);
+    };
+    const double cj = (comp && g->logw[j] != -INFINITY) ? g->logw[j] - g->logdet_half[j] - 0.5 * d * log(2 * kPi)
+                                                         : -INFINITY;
     const int shear = g->shear;
     const double mlw = J.work[kWMax], beta = J.work[kWBeta];
-    for (int64_t i = (int64_t)blockIdx.x * kEmThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kEmThreads) {
-        const double w = sample_weight((double)lw[i], mlw, beta);
-        double x[7];
+    double acc[kMom];
 #pragma unroll
-        for (int a = 0; a < 7; a++) x[a] = load_col(th, J.ld, col[a], i);   // col[a] valid: loads in flight together
-        if (shear) {
-            const double phi = (double)th[5 * J.ld + i];
+    for (int c = 0; c < kMom; c++) acc[c] = 0.0;
+    const int64_t b0 = (int64_t)blockIdx.x * Lo.tile, b1 = min(b0 + Lo.tile, J.n);
+    for (int64_t c0 = b0; c0 < b1; c0 += kEmThreads) {
+        __syncthreads();   // the previous samples are done with
+        {
+            const int64_t i = c0 + tid < b1 ? c0 + tid : b1 - 1;
+            double x[7];
+#pragma unroll
+            for (int a = 0; a < 7; a++) x[a] = load_col(th, J.ld, col[a], i);   // col[a] valid: loads in flight together
+            const double lwv = (double)lw[i];
+            if (shear) {
+                const double phi = (double)th[5 * J.ld + i];
+#pragma unroll
+                for (int a = 0; a < 7; a++)
+                    if (a < d && col[a] == 6) x[a] = shear_phase(x[a], phi, shear);
+            }
 #pragma unroll
             for (int a = 0; a < 7; a++)
-                if (a < d && col[a] == 6) x[a] = shear_phase(x[a], phi, shear);
+                if (a < d) S.x[a][tid] = x[a];
+            S.w[tid] = c0 + tid < b1 ? sample_weight(lwv, mlw, beta) : 0.0;
         }
-#pragma unroll
-        for (int a = 0; a < 7; a++) x[a] = a < d ? x[a] : 0.0;
-        double m = -INFINITY;
+        __syncthreads();
+        if (comp) {
 #pragma unroll 1
-        for (int j = 0; j < nc; j++) {
-            double lrj = -INFINITY;
-            if (s_c[j] != -INFINITY) {
-                double df[7];
+            for (int s = l; s < kEmThreads; s += LP) {
+                double df[7], q = 0.0;
 #pragma unroll
-                for (int a = 0; a < 7; a++) df[a] = a < d ? wrapd(x[a] - s_mean[j][a], P[a]) : 0.0;
-                double q = 0.0;
-                int k = 0;
+                for (int a = 0; a < 7; a++) df[a] = a < d ? off(a, S.x[a][s]) : 0.0;
 #pragma unroll
                 for (int a = 0; a < 7; a++) {
+                    if (a >= d) break;
                     double y = 0.0;
 #pragma unroll
-                    for (int b = 0; b <= a; b++) y += s_li[j][k++] * df[b];
-                    q += a < d ? y * y : 0.0;
+                    for (int b = 0; b <= a; b++) y += li[a * (a + 1) / 2 + b] * df[b];
+                    q += y * y;
                 }
-                lrj = s_c[j] - 0.5 * q;
-                m = fmax(m, lrj);
+                S.r[j][s] = cj == -INFINITY ? -INFINITY : cj - 0.5 * q;
             }
-            s_lr[j][threadIdx.x] = lrj;
         }
-        double sum = 0.0;
-#pragma unroll 1
-        for (int j = 0; j < nc; j++) {
-            const double l = s_lr[j][threadIdx.x];
-            const double e = (l == -INFINITY) ? 0.0 : exp(l - m);
-            s_lr[j][threadIdx.x] = e;
-            sum += e;
+        __syncthreads();
+        {
+            double m = -INFINITY, sum = 0.0;
+            for (int k = 0; k < nc; k++) m = fmax(m, S.r[k][tid]);
+            for (int k = 0; k < nc; k++) {
+                const double v = S.r[k][tid];
+                const double e = (v == -INFINITY) ? 0.0 : exp(v - m);
+                S.r[k][tid] = e;
+                sum += e;
+            }
+            // a sample past the tile has no weight (its x is the last one's)
+            const double scale = (m > -INFINITY && c0 + tid < b1) ? S.w[tid] / sum : 0.0;
+            for (int k = 0; k < nc; k++) S.r[k][tid] *= scale;
         }
-        const double scale = (m > -INFINITY) ? w / sum : 0.0;
+        __syncthreads();
+        if (comp) {
 #pragma unroll 1
-        for (int j = 0; j < nc; j++) R[(size_t)j * n + i] = s_lr[j][threadIdx.x] * scale;
+            for (int s = l; s < kEmThreads; s += LP) {
+                const double r = S.r[j][s];
+                double x[7];
+#pragma unroll
+                for (int a = 0; a < 7; a++) x[a] = a < d ? off(a, S.x[a][s]) : 0.0;
+                acc[0] += r;
+                // with D fixed the moments of absent dimensions are skipped:
+                // they stay 0, as the sums of r x 0 they replace
+#pragma unroll
+                for (int a = 0; a < 7; a++)
+                    if (D == 0 || a < D) {
+                        const double rx = r * x[a];
+                        acc[1 + a] += rx;
+#pragma unroll
+                        for (int b = 0; b <= a; b++) acc[8 + a * (a + 1) / 2 + b] += rx * x[b];
+                    }
+            }
+        }
+    }
+    // a component's threads are lanes of one wave
+    int base = 0, lim = kMom;
+    lane_sums<kMom, LP / 2>(acc, lane, base, lim);
+    if (comp) {
+        double *o = J.work + Lo.stat + (size_t)j * Lo.nblk * kMom + blockIdx.x;   // [component][moment][tile]
+#pragma unroll
+        for (int t = 0; t < lane_left<kMom>(LP / 2); t++)
+            if (t < lim) o[(base + t) * Lo.nblk] = acc[t];
     }
 }
 
 template <class TT, class TL, int D>
-__global__ void __launch_bounds__(kEmThreads) k_em_resp(const EmJob *__restrict__ jobs) {
-    const EmJob &J = jobs[blockIdx.z];
-    __shared__ double s_mean[kMaxComp][7], s_li[kMaxComp][28], s_c[kMaxComp];
-    __shared__ double s_lr[kMaxComp][kEmThreads];   // per-thread ln pi_j N_j, then e^{. - max}
-    if (D > 0 && J.gmm->n_dim == D)
-        em_resp_body<TT, TL, D>(J, s_mean, s_li, s_c, s_lr);
-    else
-        em_resp_body<TT, TL, 0>(J, s_mean, s_li, s_c, s_lr);
-}
-
-// W_j, first and second moments of the offsets D = wrap(x - mu_j) about the
-// current mean, per tile (one pass: the covariance centred on the mean offset
-// m_j is S2/W - m_j m_j^T, the same quantity as the centred two-pass sum)
-template <class TT, int D>
-__device__ __forceinline__ void em_stat_body(const EmJob &J) {
-    const EmLayout Lo = em_layout(J.n);
-    const GmmDev *g = J.gmm;
-    const int j = blockIdx.y;
-    const TT *__restrict__ th = (const TT *)J.theta;
-    const double *R = J.work + Lo.R;
-    const int d = D > 0 ? D : g->n_dim;
-    double mu[7], P[7];
-    int col[7];
-#pragma unroll
-    for (int a = 0; a < 7; a++) {
-        col[a] = a < d ? g->dims[a] : 0;
-        mu[a] = a < d ? g->mean[j][a] : 0.0;
-        P[a] = col_period(col[a]);
-    }
-    const int shear = g->shear;
-    double acc[36];
-#pragma unroll
-    for (int c = 0; c < 36; c++) acc[c] = 0.0;
-    const int64_t b0 = (int64_t)blockIdx.x * kEmTile, b1 = min(b0 + kEmTile, J.n);
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += kEmThreads) {
-        const double r = R[(size_t)j * J.n + i];
-        // all seven column loads first (col[a] is a valid column, 0 beyond
-        // d), so that they are in flight together
-        double v[7];
-#pragma unroll
-        for (int a = 0; a < 7; a++) v[a] = load_col(th, J.ld, col[a], i);
-        if (shear) {
-            const double phi = (double)th[5 * J.ld + i];
-#pragma unroll
-            for (int a = 0; a < 7; a++)
-                if (a < d && col[a] == 6) v[a] = shear_phase(v[a], phi, shear);
-        }
-        double x[7];
-#pragma unroll
-        for (int a = 0; a < 7; a++) x[a] = (a < d) ? wrapd(v[a] - mu[a], P[a]) : 0.0;
-        acc[0] += r;
-        int k = 1;
-        // with D fixed the moments of absent dimensions are skipped: they
-        // stay 0, as the sums of r x 0 they replace
-#pragma unroll
-        for (int a = 0; a < 7; a++, k++)
-            if (D == 0 || a < D) acc[k] += r * x[a];
-#pragma unroll
-        for (int a = 0; a < 7; a++)
-#pragma unroll
-            for (int b = 0; b <= a; b++, k++)
-                if (D == 0 || a < D) acc[k] += r * x[a] * x[b];
-    }
-    block_sum<36>(acc, J.work + Lo.stat + ((size_t)j * Lo.nblk + blockIdx.x) * 36);
-}
-
-template <class TT, int D>
-__global__ void __launch_bounds__(kEmThreads) k_em_stat(const EmJob *__restrict__ jobs) {
+__global__ void __launch_bounds__(kEmThreads) k_em_pass(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
     const EmLayout Lo = em_layout(J.n);
-    if (blockIdx.x >= Lo.nblk || (int)blockIdx.y >= J.gmm->n_comp) return;
-    if (D > 0 && J.gmm->n_dim == D)
-        em_stat_body<TT, D>(J);
+    if (blockIdx.x >= Lo.nblk) return;
+    __shared__ EmShared S;
+    const int nc = J.gmm->n_comp;
+    if (blockIdx.x == 0 && threadIdx.x == 0) J.gmm->valid = 1;   // the update clears it if a factor fails
+    auto go = [&](auto D_) {
+        constexpr int DD = decltype(D_)::value;
+        if (nc <= 4)
+            em_pass<TT, TL, DD, 4>(J, Lo, S);
+        else if (nc <= 8)
+            em_pass<TT, TL, DD, 8>(J, Lo, S);
+        else
+            em_pass<TT, TL, DD, 16>(J, Lo, S);
+    };
+    bool same = D > 0 && J.gmm->n_dim == D;
+#pragma unroll
+    for (int a = 0; a < 7; a++) same = same && (a >= D || J.gmm->dims[a] == mix_col(D, a));
+    if (same)
+        go(std::integral_constant<int, D>{});
     else
-        em_stat_body<TT, 0>(J);
+        go(std::integral_constant<int, 0>{});
 }
 
 // M-step: weights, means (old mean + offset, wrapped into the period),
-// covariances + floor, then the factorisation
-__global__ void k_em_update(const EmJob *__restrict__ jobs) {
+// covariances + floor, then the factorisation.  One block per component: its
+// tiles' moments (74 KB at 256 tiles) are what it waits for, and one block
+// for all of a job's components was bound by one CU's read rate (24 us
+// against 10.5; 35 us with one thread per component).  Four waves sum nine moments each and four components'
+// weights; the first goes on alone.
+__global__ void __launch_bounds__(256) k_em_update(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
     const EmLayout Lo = em_layout(J.n);
     GmmDev *g = J.gmm;
-    const int j = threadIdx.x;
-    __shared__ double W[kMaxComp];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, j = blockIdx.x;
     const int nc = g->n_comp, d = g->n_dim;
-    double s[36];
-    for (int c = 0; c < 36; c++) s[c] = 0.0;
-    if (j < nc)
-        for (int64_t b = 0; b < Lo.nblk; b++)
-            for (int c = 0; c < 36; c++) s[c] += J.work[Lo.stat + ((size_t)j * Lo.nblk + b) * 36 + c];
-    if (j < kMaxComp) W[j] = (j < nc) ? s[0] : 0.0;
-    if (j == 0) g->valid = 1;
-    __syncthreads();
     if (j >= nc) return;
+    __shared__ double s[kMom], W[kMaxComp];
+    const double *st = J.work + Lo.stat;
+    constexpr int kPer = kMom / 4;
+    tile_sums<kPer>(st + ((size_t)j * kMom + wv * kPer) * Lo.nblk, Lo.nblk, lane, s + wv * kPer);
+    for (int q = wv; q < nc; q += 4) tile_sums<1>(st + (size_t)q * kMom * Lo.nblk, Lo.nblk, lane, W + q);
+    if (j == 0 && threadIdx.x < kMaxComp) J.zcount[threadIdx.x] = 0u;   // for the mass estimate after the last iteration
+    __syncthreads();
+    if (wv != 0) return;
     double tot = 0.0;
     for (int q = 0; q < nc; q++) tot += W[q];
-    g->w[j] = s[0] / tot;
-    if (s[0] > 0.0) {
-        const double Wj = s[0];
-        double m[7];
-        for (int a = 0; a < 7; a++) m[a] = a < d ? s[1 + a] / Wj : 0.0;
-        int k = 8;
-        for (int a = 0; a < 7; a++)
-            for (int b = 0; b <= a; b++) {
-                const double v = (a < d && b < d) ? s[k] / Wj - m[a] * m[b] : 0.0;
-                k++;
-                g->cov[j][a][b] = v;
-                g->cov[j][b][a] = v;
-            }
-        for (int a = 0; a < d; a++) {
-            const double rg = col_range(J.pr, g->dims[a]);
-            g->cov[j][a][a] += 1e-8 * rg * rg;
-            double mu = g->mean[j][a] + m[a];
-            const double P = col_period(g->dims[a]);
+    const double Wj = s[0];
+    if (lane == 0) g->w[j] = Wj / tot;
+    double row[7], m = 0.0;
+    if (Wj > 0.0) {
+        wave_cov(s, J.pr, *g, lane, d, row, m);
+        if (lane < 7)
+            for (int b = 0; b < 7; b++) g->cov[j][lane][b] = row[b];
+        if (lane < d) {
+            double mu = g->mean[j][lane] + m;
+            const double P = col_period(g->dims[lane]);
             if (P > 0.0) mu = mu - P * floor(mu / P);
-            g->mean[j][a] = mu;
+            g->mean[j][lane] = mu;
         }
+    } else {
+#pragma unroll
+        for (int b = 0; b < 7; b++) row[b] = lane < 7 ? g->cov[j][lane][b] : 0.0;
     }
-    factor_one(*g, j);
+    __threadfence_block();
+    wave_factor(*g, j, lane, d, row);
 }
 
 template <class TT, class TL, int D>
-void launch_em_t(const EmJob *d_jobs, int n_jobs, int64_t nblk_max, int64_t rblk, bool any_first, int n_iter,
-                 hipStream_t st) {
+void launch_em_t(const EmJob *d_jobs, int n_jobs, int64_t nblk_max, bool any_first, int n_iter, hipStream_t st) {
     const dim3 jz(1, 1, n_jobs), tiles(nblk_max, 1, n_jobs);
     hipLaunchKernelGGL((k_em_scan<TL>), tiles, dim3(kEmThreads), 0, st, d_jobs);
-    hipLaunchKernelGGL(k_em_scan_final, jz, dim3(64), 0, st, d_jobs);
     hipLaunchKernelGGL((k_em_beta<TL>), tiles, dim3(kEmThreads), 0, st, d_jobs);
-    hipLaunchKernelGGL(k_em_beta_final, jz, dim3(64), 0, st, d_jobs);
+    hipLaunchKernelGGL(k_em_beta_final, jz, dim3(256), 0, st, d_jobs);
     if (any_first) {
-        hipLaunchKernelGGL((k_em_top<TL>), tiles, dim3(kTopThreads), 0, st, d_jobs);
-        hipLaunchKernelGGL((k_em_top_final<TT>), jz, dim3(256), 0, st, d_jobs);
+        hipLaunchKernelGGL((k_em_top<TL>), tiles, dim3(kEmThreads), 0, st, d_jobs);
+        hipLaunchKernelGGL((k_em_top_final<TT>), jz, dim3(kEmThreads), 0, st, d_jobs);
         hipLaunchKernelGGL((k_em_init<TT, TL>), tiles, dim3(kEmThreads), 0, st, d_jobs);
-        hipLaunchKernelGGL(k_em_init_final, jz, dim3(64), 0, st, d_jobs);
-        hipLaunchKernelGGL(k_gmm_factor, jz, dim3(64), 0, st, d_jobs, 1);
+        hipLaunchKernelGGL(k_em_init_final, jz, dim3(64 * kMaxComp), 0, st, d_jobs);
     }
-    const dim3 comp(nblk_max, kMaxComp, n_jobs);
     for (int it = 0; it < n_iter; it++) {
-        hipLaunchKernelGGL((k_em_resp<TT, TL, D>), dim3(rblk, 1, n_jobs), dim3(kEmThreads), 0, st, d_jobs);
-        hipLaunchKernelGGL((k_em_stat<TT, D>), comp, dim3(kEmThreads), 0, st, d_jobs);
-        hipLaunchKernelGGL(k_em_update, jz, dim3(64), 0, st, d_jobs);
+        hipLaunchKernelGGL((k_em_pass<TT, TL, D>), tiles, dim3(kEmThreads), 0, st, d_jobs);
+        hipLaunchKernelGGL(k_em_update, dim3(kMaxComp, 1, n_jobs), dim3(256), 0, st, d_jobs);
     }
 }
 
@@ -701,7 +821,7 @@ size_t em_work_bytes(int64_t n) { return em_layout(n).total * sizeof(double); }
 
 hipError_t launch_gmm_factor(const EmJob *d_jobs, int n_jobs, hipStream_t st) {
     if (n_jobs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gmm_factor, dim3(1, 1, n_jobs), dim3(64), 0, st, d_jobs, 0);
+    hipLaunchKernelGGL(k_gmm_factor, dim3(1, 1, n_jobs), dim3(64 * kMaxComp), 0, st, d_jobs);
     return hipGetLastError();
 }
 
@@ -709,16 +829,13 @@ hipError_t launch_em_batch(int policy, const EmJob *d_jobs, const EmJob *h_jobs,
                            hipStream_t st) {
     if (n_jobs <= 0) return hipSuccess;
     if (n_jobs > 65535) return hipErrorInvalidValue;
-    int64_t nblk_max = 1, nmax = 1;
+    int64_t nblk_max = 1;
     bool any_first = false;
     for (int k = 0; k < n_jobs; k++) {
         if (h_jobs[k].n < 1) return hipErrorInvalidValue;
         nblk_max = std::max<int64_t>(nblk_max, em_layout(h_jobs[k].n).nblk);
-        nmax = std::max<int64_t>(nmax, h_jobs[k].n);
         any_first = any_first || h_jobs[k].first;
     }
-    const int64_t rblk = std::min<int64_t>((nmax + kEmThreads - 1) / kEmThreads, 4096);
-    if (nblk_max > INT32_MAX) return hipErrorInvalidValue;
     // the mixtures' dimension count, when every job of the batch shares it
     // (each mixture takes its job's default columns; the kernels check)
     int dim = h_jobs[0].n_dim;
@@ -727,11 +844,11 @@ hipError_t launch_em_batch(int policy, const EmJob *d_jobs, const EmJob *h_jobs,
     auto go = [&](auto D_) {
         constexpr int D = decltype(D_)::value;
         if (policy == kFP64)
-            launch_em_t<double, double, D>(d_jobs, n_jobs, nblk_max, rblk, any_first, n_iter, st);
+            launch_em_t<double, double, D>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
         else if (policy == kFP32)
-            launch_em_t<float, float, D>(d_jobs, n_jobs, nblk_max, rblk, any_first, n_iter, st);
+            launch_em_t<float, float, D>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
         else
-            launch_em_t<float, double, D>(d_jobs, n_jobs, nblk_max, rblk, any_first, n_iter, st);
+            launch_em_t<float, double, D>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
     };
     if (dim == 6)
         go(std::integral_constant<int, 6>{});

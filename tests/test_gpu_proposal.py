@@ -211,6 +211,34 @@ def test_em_mixture_matches_oracle(orc, policy, temper):
         assert np.allclose(gc, c, rtol=1e-6, atol=1e-12)
 
 
+@pytest.mark.parametrize("n,n_comp", [
+    (300, 1), (511, 4),             # one tile, two; components in groups of 64 threads
+    (257, 5), (65536, 8),           # a tile of one sample; 256 tiles of one block; groups of 32
+    (65537, 9), (140001, 16),       # tiles of two and three blocks; groups of 16
+])
+def test_em_tiles_and_component_groups(orc, n, n_comp):
+    """First fit and two iterations at the edges of the sample tiles (at most
+    256, whole blocks of 256 samples) and of the component counts that share a
+    thread layout (4, 8, 16), with infinite and NaN weights among the samples."""
+    th, lw = _weighted_samples(n, 45 + n_comp, ile.ILE_FP64)
+    lw[n // 3] = -np.inf
+    lw[n // 2] = np.nan
+    job, _ = _job(ile.ILE_FP64)
+    try:
+        p = ile.ile_adapt_proposal(job, n, torch.from_numpy(th).cuda(), n, torch.from_numpy(lw).cuda(),
+                                   ile.gmm_opts(n_comp=n_comp, n_iter=2, temper_ess=1.0 / 16.0))
+    finally:
+        ile.ile_job_release(job)
+    lw64 = np.where(np.isfinite(lw), lw, -np.inf)
+    w, m, c = orc.em_fit(th, lw64, list(range(7)), n_iter=2, n_comp=n_comp, temper_ess=1.0 / 16.0)
+    gw = np.array([p.weight[j] for j in range(n_comp)])
+    gm = np.array([[p.mean[j][a] for a in range(7)] for j in range(n_comp)])
+    gc = np.array([[[p.cov[j][a][b] for b in range(7)] for a in range(7)] for j in range(n_comp)])
+    assert np.allclose(gw, w, rtol=1e-8, atol=1e-11)
+    assert np.allclose(gm, m, rtol=1e-8, atol=1e-10)
+    assert np.allclose(gc, c, rtol=1e-7, atol=1e-12)
+
+
 @pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32])
 def test_em_first_fit_with_duplicates_matches_oracle(orc, policy):
     """Duplicate-heavy samples (as fair redraws produce): the 24 highest-weight
