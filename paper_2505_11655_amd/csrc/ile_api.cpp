@@ -1000,9 +1000,19 @@ ile_status batch_done(ile_ctx *ctx, int slot, hipStream_t st) {
     return ILE_OK;
 }
 
+// Samples per block of a draw launch: four blocks per CU over the whole launch
+// (a draw of 2^16 samples at 2,048 per block ran on 32 CUs), whole blocks of 256
+// threads, at most 2,048.  A sample's draw does not depend on its block.
+static int64_t draw_tile(int64_t total) {
+    const int64_t t = (total + 1023) / 1024;
+    return std::min<int64_t>(2048, std::max<int64_t>(256, (t + 255) / 256 * 256));
+}
+
 // Counter-based draws for several jobs of one theta type in one launch.
 ile_status draw_batch(ile_ctx *ctx, int policy, const std::vector<DrawJob> &jobs, hipStream_t st) {
-    const int64_t tile = 2048;
+    int64_t total = 0;
+    for (const DrawJob &j : jobs) total += j.n;
+    const int64_t tile = draw_tile(total);
     std::vector<Tile> tiles;
     for (size_t j = 0; j < jobs.size(); j++)
         for (int64_t t = 0; t < jobs[j].n; t += tile) tiles.push_back(Tile{(int32_t)j, 0, t, std::min(t + tile, jobs[j].n)});
@@ -1127,7 +1137,7 @@ extern "C" ile_status ile_draw(ile_job *job, uint64_t seed, uint32_t round, int6
     dj.ld = ld;
     dj.lnpmps = lnpmps_out;
     dj.n = n;
-    const int64_t tile = 2048;
+    const int64_t tile = draw_tile(n);
     const int64_t nt = (n + tile - 1) / tile;
     if (nt > INT32_MAX) return set_err(ILE_E_INVALID, "too many samples for one launch");
     hipError_t e =

@@ -590,11 +590,8 @@ __global__ void __launch_bounds__(64 * kMaxComp) k_gmm_factor(const EmJob *__res
 // The responsibilities never leave the CU.  Latency and FP64 issue bound it:
 // 2^16 samples, 8 components, 6 dimensions: 11.7 us, where responsibilities
 // through memory and moments of 8,192-sample tiles took 13.8 + 28.4 us.
-// The kernel takes the mixture's columns as compile-time constants for the two
-// default sets (D = 6: all but the distance, D = 7: all; D = 0: read at run
-// time), which removes the per-dimension tests and the periods' registers from
-// the unrolled loops; compiled for D it checks the mixture's columns and runs
-// the general body for any others.
+// A mixture spans its job's sampled columns, all seven (D = 7) or all but the
+// distance (D = 6): columns and periods are compile-time constants.
 constexpr int mix_col(int D, int a) { return D == 6 && a >= 3 ? a + 1 : a; }
 constexpr double mix_period(int D, int a) {
     const int c = mix_col(D, a);
@@ -617,25 +614,21 @@ __device__ __forceinline__ void em_pass(const EmJob &J, const EmLayout &Lo, EmSh
     const TT *__restrict__ th = (const TT *)J.theta;
     const TL *__restrict__ lw = (const TL *)J.lw;
     const GmmDev *g = J.gmm;
-    const int d = D > 0 ? D : g->n_dim, nc = g->n_comp;
+    const int nc = g->n_comp;
     const int tid = threadIdx.x, lane = tid & 63, j = tid / LP, l = tid % LP;
     const bool comp = j < nc;
-    int col[7];
-    double P[7], iP[7], mu[7], li[28];
+    double mu[D], li[D * (D + 1) / 2];
 #pragma unroll
-    for (int a = 0; a < 7; a++) {
-        col[a] = D > 0 ? mix_col(D, a < D ? a : 0) : (a < d ? g->dims[a] : 0);
-        P[a] = D > 0 ? mix_period(D, a) : (a < d ? col_period(col[a]) : 0.0);
-        iP[a] = P[a] > 0.0 ? 1.0 / P[a] : 0.0;
-        mu[a] = comp && a < d ? g->mean[j][a] : 0.0;
+    for (int a = 0; a < D; a++) {
+        mu[a] = comp ? g->mean[j][a] : 0.0;
 #pragma unroll
-        for (int b = 0; b <= a; b++) li[a * (a + 1) / 2 + b] = comp && a < d ? g->Linv[j][a][b] : 0.0;
+        for (int b = 0; b <= a; b++) li[a * (a + 1) / 2 + b] = comp ? g->Linv[j][a][b] : 0.0;
     }
     auto off = [&](int a, double v) {   // wrapped offset from the component's mean
-        const double u = v - mu[a];
-        return (D > 0 && mix_period(D, a) == 0.0) ? u : wrapn(u, P[a], iP[a]);
+        const double u = v - mu[a], P = mix_period(D, a);
+        return P > 0.0 ? wrapn(u, P, 1.0 / P) : u;
     };
-    const double cj = (comp && g->logw[j] != -INFINITY) ? g->logw[j] - g->logdet_half[j] - 0.5 * d * log(2 * kPi)
+    const double cj = (comp && g->logw[j] != -INFINITY) ? g->logw[j] - g->logdet_half[j] - 0.5 * D * log(2 * kPi)
                                                          : -INFINITY;
     const int shear = g->shear;
     const double mlw = J.work[kWMax], beta = J.work[kWBeta];
@@ -647,31 +640,24 @@ __device__ __forceinline__ void em_pass(const EmJob &J, const EmLayout &Lo, EmSh
         __syncthreads();   // the previous samples are done with
         {
             const int64_t i = c0 + tid < b1 ? c0 + tid : b1 - 1;
-            double x[7];
+            double x[D];
 #pragma unroll
-            for (int a = 0; a < 7; a++) x[a] = load_col(th, J.ld, col[a], i);   // col[a] valid: loads in flight together
+            for (int a = 0; a < D; a++) x[a] = load_col(th, J.ld, mix_col(D, a), i);
             const double lwv = (double)lw[i];
-            if (shear) {
-                const double phi = (double)th[5 * J.ld + i];
+            if (shear) x[D - 1] = shear_phase(x[D - 1], x[D - 2], shear);   // psi by phi_c
 #pragma unroll
-                for (int a = 0; a < 7; a++)
-                    if (a < d && col[a] == 6) x[a] = shear_phase(x[a], phi, shear);
-            }
-#pragma unroll
-            for (int a = 0; a < 7; a++)
-                if (a < d) S.x[a][tid] = x[a];
+            for (int a = 0; a < D; a++) S.x[a][tid] = x[a];
             S.w[tid] = c0 + tid < b1 ? sample_weight(lwv, mlw, beta) : 0.0;
         }
         __syncthreads();
         if (comp) {
 #pragma unroll 1
             for (int s = l; s < kEmThreads; s += LP) {
-                double df[7], q = 0.0;
+                double df[D], q = 0.0;
 #pragma unroll
-                for (int a = 0; a < 7; a++) df[a] = a < d ? off(a, S.x[a][s]) : 0.0;
+                for (int a = 0; a < D; a++) df[a] = off(a, S.x[a][s]);
 #pragma unroll
-                for (int a = 0; a < 7; a++) {
-                    if (a >= d) break;
+                for (int a = 0; a < D; a++) {
                     double y = 0.0;
 #pragma unroll
                     for (int b = 0; b <= a; b++) y += li[a * (a + 1) / 2 + b] * df[b];
@@ -699,20 +685,18 @@ __device__ __forceinline__ void em_pass(const EmJob &J, const EmLayout &Lo, EmSh
 #pragma unroll 1
             for (int s = l; s < kEmThreads; s += LP) {
                 const double r = S.r[j][s];
-                double x[7];
+                double x[D];
 #pragma unroll
-                for (int a = 0; a < 7; a++) x[a] = a < d ? off(a, S.x[a][s]) : 0.0;
+                for (int a = 0; a < D; a++) x[a] = off(a, S.x[a][s]);
                 acc[0] += r;
-                // with D fixed the moments of absent dimensions are skipped:
-                // they stay 0, as the sums of r x 0 they replace
+                // the moments of an absent dimension stay 0
 #pragma unroll
-                for (int a = 0; a < 7; a++)
-                    if (D == 0 || a < D) {
-                        const double rx = r * x[a];
-                        acc[1 + a] += rx;
+                for (int a = 0; a < D; a++) {
+                    const double rx = r * x[a];
+                    acc[1 + a] += rx;
 #pragma unroll
-                        for (int b = 0; b <= a; b++) acc[8 + a * (a + 1) / 2 + b] += rx * x[b];
-                    }
+                    for (int b = 0; b <= a; b++) acc[8 + a * (a + 1) / 2 + b] += rx * x[b];
+                }
             }
         }
     }
@@ -727,7 +711,7 @@ __device__ __forceinline__ void em_pass(const EmJob &J, const EmLayout &Lo, EmSh
     }
 }
 
-template <class TT, class TL, int D>
+template <class TT, class TL>
 __global__ void __launch_bounds__(kEmThreads) k_em_pass(const EmJob *__restrict__ jobs) {
     const EmJob &J = jobs[blockIdx.z];
     const EmLayout Lo = em_layout(J.n);
@@ -736,21 +720,18 @@ __global__ void __launch_bounds__(kEmThreads) k_em_pass(const EmJob *__restrict_
     const int nc = J.gmm->n_comp;
     if (blockIdx.x == 0 && threadIdx.x == 0) J.gmm->valid = 1;   // the update clears it if a factor fails
     auto go = [&](auto D_) {
-        constexpr int DD = decltype(D_)::value;
+        constexpr int D = decltype(D_)::value;
         if (nc <= 4)
-            em_pass<TT, TL, DD, 4>(J, Lo, S);
+            em_pass<TT, TL, D, 4>(J, Lo, S);
         else if (nc <= 8)
-            em_pass<TT, TL, DD, 8>(J, Lo, S);
+            em_pass<TT, TL, D, 8>(J, Lo, S);
         else
-            em_pass<TT, TL, DD, 16>(J, Lo, S);
+            em_pass<TT, TL, D, 16>(J, Lo, S);
     };
-    bool same = D > 0 && J.gmm->n_dim == D;
-#pragma unroll
-    for (int a = 0; a < 7; a++) same = same && (a >= D || J.gmm->dims[a] == mix_col(D, a));
-    if (same)
-        go(std::integral_constant<int, D>{});
+    if (J.gmm->n_dim == 6)
+        go(std::integral_constant<int, 6>{});
     else
-        go(std::integral_constant<int, 0>{});
+        go(std::integral_constant<int, 7>{});
 }
 
 // M-step: weights, means (old mean + offset, wrapped into the period),
@@ -797,7 +778,7 @@ __global__ void __launch_bounds__(256) k_em_update(const EmJob *__restrict__ job
     wave_factor(*g, j, lane, d, row);
 }
 
-template <class TT, class TL, int D>
+template <class TT, class TL>
 void launch_em_t(const EmJob *d_jobs, int n_jobs, int64_t nblk_max, bool any_first, int n_iter, hipStream_t st) {
     const dim3 jz(1, 1, n_jobs), tiles(nblk_max, 1, n_jobs);
     hipLaunchKernelGGL((k_em_scan<TL>), tiles, dim3(kEmThreads), 0, st, d_jobs);
@@ -810,7 +791,7 @@ void launch_em_t(const EmJob *d_jobs, int n_jobs, int64_t nblk_max, bool any_fir
         hipLaunchKernelGGL(k_em_init_final, jz, dim3(64 * kMaxComp), 0, st, d_jobs);
     }
     for (int it = 0; it < n_iter; it++) {
-        hipLaunchKernelGGL((k_em_pass<TT, TL, D>), tiles, dim3(kEmThreads), 0, st, d_jobs);
+        hipLaunchKernelGGL((k_em_pass<TT, TL>), tiles, dim3(kEmThreads), 0, st, d_jobs);
         hipLaunchKernelGGL(k_em_update, dim3(kMaxComp, 1, n_jobs), dim3(256), 0, st, d_jobs);
     }
 }
@@ -836,26 +817,12 @@ hipError_t launch_em_batch(int policy, const EmJob *d_jobs, const EmJob *h_jobs,
         nblk_max = std::max<int64_t>(nblk_max, em_layout(h_jobs[k].n).nblk);
         any_first = any_first || h_jobs[k].first;
     }
-    // the mixtures' dimension count, when every job of the batch shares it
-    // (each mixture takes its job's default columns; the kernels check)
-    int dim = h_jobs[0].n_dim;
-    for (int k = 1; k < n_jobs; k++)
-        if (h_jobs[k].n_dim != dim) dim = 0;
-    auto go = [&](auto D_) {
-        constexpr int D = decltype(D_)::value;
-        if (policy == kFP64)
-            launch_em_t<double, double, D>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
-        else if (policy == kFP32)
-            launch_em_t<float, float, D>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
-        else
-            launch_em_t<float, double, D>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
-    };
-    if (dim == 6)
-        go(std::integral_constant<int, 6>{});
-    else if (dim == 7)
-        go(std::integral_constant<int, 7>{});
+    if (policy == kFP64)
+        launch_em_t<double, double>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
+    else if (policy == kFP32)
+        launch_em_t<float, float>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
     else
-        go(std::integral_constant<int, 0>{});
+        launch_em_t<float, double>(d_jobs, n_jobs, nblk_max, any_first, n_iter, st);
     return hipGetLastError();
 }
 

@@ -76,6 +76,29 @@ def test_proposal_mass_and_draws(orc, policy, outside):
     assert abs(r.mean() - 1) < 4 * r.std() / math.sqrt(n) + 2e-3
 
 
+@pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32])
+def test_mixture_draws_do_not_depend_on_the_launch(policy):
+    """One launch of 2^21 + 5 mixture draws (2,048 samples per block; retries
+    and prior draws queue up in it, component three rejects most attempts)
+    equals launches of 1, 257 and 3,001 draws (256 per block) at the same
+    sample indices to the bit."""
+    job, _ = _job(policy)
+    try:
+        ile.ile_set_proposal(job, ile.gmm_params([0.3, 0.2, 0.5], MEANS + [MEAN_OUT], COVS + [COV_OUT]))
+        n, dt = (1 << 21) + 5, gu.torch_dtype(policy)
+        th = torch.empty((7, n), dtype=dt, device="cuda")
+        lr = torch.empty((n,), dtype=dt, device="cuda")
+        ile.ile_draw(job, 5, 2, 11, n, th, n, lr)
+        for first, m in ((0, 1), (2047, 257), (1 << 20, 3001), (n - 5, 5)):
+            t2 = torch.empty((7, m), dtype=dt, device="cuda")
+            l2 = torch.empty((m,), dtype=dt, device="cuda")
+            ile.ile_draw(job, 5, 2, 11 + first, m, t2, m, l2)
+            torch.cuda.synchronize()
+            assert torch.equal(t2, th[:, first:first + m]) and torch.equal(l2, lr[first:first + m])
+    finally:
+        ile.ile_job_release(job)
+
+
 @pytest.mark.parametrize("shear", [1, -1])
 @pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32])
 def test_sheared_proposal_draws(orc, policy, shear):
