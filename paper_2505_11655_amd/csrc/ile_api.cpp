@@ -109,22 +109,33 @@ bool job_lds_ok(const ile_job *job, bool tmarg) {
     return compiled && job_window_bytes(job, tmarg) <= eval_lds_limit();
 }
 
-// Launch geometry of one eval over n samples of a job (single-job path).
-void eval_geometry(const ile_job *job, int64_t n, size_t *lds, int64_t *tile, int *block) {
-    const size_t win = job_window_bytes(job, false);
-    const int64_t cus = 256;
-    // stage the window in LDS only when each block gets enough samples to pay for it
-    if (job_lds_ok(job, false) && n >= (int64_t)2 * cus * 16384) {
-        *lds = win;
-        *block = lds_block_threads(job->set, job->policy);
-        *tile = std::max<int64_t>(16384, (n + 2 * cus - 1) / (2 * cus));
-    } else {
-        *lds = 0;
-        *block = 256;
-        int64_t t = (n + 4 * cus - 1) / (4 * cus);
-        t = ((t + 255) / 256) * 256;
-        *tile = std::min<int64_t>(std::max<int64_t>(t, 256), 8192);
+// Samples per block of an LDS-staged launch: every block stages its job's
+// window (the time of about kStage samples), one block runs per CU, and a tile
+// belongs to one job.  Of 1, 2, 4 and 8 rounds over the 256 CUs, the one whose
+// smallest tile that fits costs least; 0 when that tile is below 512 samples.
+static int64_t staged_tile(const std::vector<int64_t> &n) {
+    constexpr int64_t kCus = 256, kStage = 300;
+    int64_t total = 0;
+    for (int64_t v : n) total += v;
+    int64_t best = 0, best_cost = INT64_MAX;
+    for (int64_t r = 1; r <= 8; r *= 2) {
+        int64_t t = (total / (kCus * r) + 255) / 256 * 256;
+        t = std::max<int64_t>(t, 256);
+        for (;; t = (t + t / 16 + 255) / 256 * 256) {
+            int64_t tiles = 0;
+            for (int64_t v : n) tiles += (v + t - 1) / t;
+            // as many rounds as the jobs alone ask for when they are more than the tiles aimed at
+            const int64_t rounds = (tiles + kCus - 1) / kCus;
+            if (rounds <= r || tiles == (int64_t)n.size()) {
+                if (rounds * (t + kStage) < best_cost) {
+                    best_cost = rounds * (t + kStage);
+                    best = t;
+                }
+                break;
+            }
+        }
     }
+    return best >= 512 ? best : 0;
 }
 
 ile_status ctx_check(ile_ctx *ctx) {
@@ -895,6 +906,21 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
     return ILE_OK;
 }
 
+// Blocks go to the eight XCDs in turn, each with an L2 of its own: give every
+// XCD a run of consecutive tiles, so that it reads the windows of its own jobs
+// only.
+static void xcd_order(std::vector<Tile> &tiles) {
+    constexpr size_t kXcds = 8;
+    const size_t n = tiles.size(), per = n / kXcds, extra = n % kXcds;
+    if (per == 0) return;
+    std::vector<Tile> out(n);
+    for (size_t h = 0; h < n; h++) {
+        const size_t x = h % kXcds;   // XCD x takes per (+ 1 for the first `extra`) tiles from its start
+        out[h] = tiles[x * per + std::min(x, extra) + h / kXcds];
+    }
+    tiles.swap(out);
+}
+
 // Group jobs by compiled kernel, upload the descriptors and tile lists through
 // the context's pinned staging buffer, and launch one kernel per group.
 ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStream_t st) {
@@ -910,18 +936,22 @@ ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStre
         int64_t total = 0;
         size_t win = 0;
         bool lds_ok = true;
+        std::vector<int64_t> ns;
         for (int i : idx) {
             total += items[i].n;
             const ile_job *j = items[i].job;
             win = std::max(win, job_window_bytes(j, false));
             lds_ok = lds_ok && job_lds_ok(j, false);
+            ns.push_back(items[i].n);
         }
+        // LDS-staged from 512 samples per CU up (2^17 samples, HLV 9 modes: FP32
+        // 22 against 24 us unstaged, FP64 30 against 39; 2^20: 68 against 104,
+        // 114 against 236).  Below, and where no window fits: about four
+        // 256-thread blocks per CU over the whole batch (small batches would
+        // otherwise leave most CUs idle), 256 to 8192 samples per tile.
         const int64_t cus = 256;
-        const bool lds = lds_ok && total >= (int64_t)2 * cus * 16384 && total / (int64_t)idx.size() >= 65536;
-        // without LDS staging: about four 256-thread blocks per CU over the
-        // whole batch (small batches would otherwise leave most CUs idle),
-        // 256 to 8192 samples per tile
-        int64_t tile = 65536;
+        int64_t tile = lds_ok && total >= cus * 512 ? staged_tile(ns) : 0;
+        const bool lds = tile > 0;
         if (!lds) {
             tile = (total + 4 * cus - 1) / (4 * cus);
             tile = std::min<int64_t>(std::max<int64_t>((tile + 255) / 256 * 256, 256), 8192);
@@ -941,6 +971,7 @@ ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStre
             ej.push_back(e);
             for (int64_t t0 = 0; t0 < b.n; t0 += tile) tiles.push_back(Tile{jid, 0, t0, std::min(t0 + tile, b.n)});
         }
+        xcd_order(tiles);
         void *dj = nullptr, *dt = nullptr;
         int slot = -1;
         ile_status s = batch_upload(ctx, ej.data(), ej.size() * sizeof(EvalJob), tiles.data(),

@@ -221,7 +221,6 @@ ile_status av_batch(ile_ctx *ctx, bool update, int policy, const std::vector<AvJ
 // on first use), and batched draws / updates as for AV.
 ile_status ac_ensure(ile_job *job, hipStream_t st);
 ile_status ac_batch(ile_ctx *ctx, bool update, int policy, const std::vector<AcJob> &jobs, hipStream_t st);
-void eval_geometry(const ile_job *job, int64_t n, size_t *lds, int64_t *tile, int *block);
 size_t theta_size(int policy);
 size_t out_size(int policy);
 // Samples per stage-1 tile of the estimator for a job of n samples: at least

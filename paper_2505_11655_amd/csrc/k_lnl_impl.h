@@ -337,6 +337,15 @@ struct LnlKernel {
                 }
             }
         });
+        // The V groups form the pair products again from y as redefined here:
+        // kept from the U groups (the same values) they hold P registers
+        // (twice that in FP64) across the whole form and cost the occupancy.
+        TG yv[NM];
+#pragma unroll
+        for (int a = 0; a < NM; a++) {
+            yv[a] = y[a];
+            if constexpr (MS::P * (sizeof(TA) / 4) > 64) asm volatile("" : "+v"(yv[a]));
+        }
         static_for<0, 4 * LM + 1>([&](auto G_) {
             constexpr int g = decltype(G_)::value;
             fence();
@@ -351,7 +360,7 @@ struct LnlKernel {
                 static_for<pt.v_start[g], pt.v_start[g + 1]>([&](auto J_) {
                     constexpr int j = decltype(J_)::value;
                     constexpr int p = pt.v_pair[j];
-                    const TA py = (TA)y[pt.a[p]] * (TA)y[pt.b[p]];
+                    const TA py = (TA)yv[pt.a[p]] * (TA)yv[pt.b[p]];
 #pragma unroll
                     for (int k = 0; k < K; k++) {
                         Br[k] += py * Vt[j * K + k].re;
@@ -457,6 +466,9 @@ struct LnlKernel {
                 static_for<0, NM>([&](auto A_) {
                     constexpr int a = decltype(A_)::value;
                     constexpr int m = kSets[S].m[a];
+                    // FP64: the taps of three modes in flight at a time (left to
+                    // itself the scheduler holds every mode's)
+                    if constexpr (sizeof(TA) == 8 && a % 3 == 0) fence();
                     const cpx<TA> q0 = q[a], q1 = q[NM + a], q2 = q[2 * NM + a], q3 = q[3 * NM + a];
                     const TA qr = w0 * q0.re + w1 * q1.re + w2 * q2.re + w3 * q3.re;
                     const TA qi = w0 * q0.im + w1 * q1.im + w2 * q2.im + w3 * q3.im;
@@ -491,12 +503,11 @@ struct LnlKernel {
     }
 };
 
-// Minimum waves per SIMD asked of the register allocator: two, except for the
-// 17/21-mode sets with FP64 contractions and the 21-mode set in FP32, whose
-// live state does not fit in 256 VGPRs without spilling.
+// Minimum waves per SIMD asked of the register allocator: those of one
+// LDS-staged block per CU; the unstaged variant reaches at least as many.
 template <int S, int POL>
 constexpr int lnl_min_waves() {
-    return ((S >= 2 && POL != kFP32) || S == 3) ? 1 : 2;
+    return lds_block_threads(S, POL) / 256;
 }
 
 template <int S, int K, int POL, bool LDS, bool DM>

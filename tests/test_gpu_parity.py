@@ -373,6 +373,39 @@ def test_eval_batch_equals_single(policy):
         ile.ile_job_release(job)
 
 
+@pytest.mark.parametrize("policy", POLICIES, ids=[PNAME[p] for p in POLICIES])
+@pytest.mark.parametrize("modes,sizes", [
+    (5, [131072]), (9, [131071]),                  # the smallest staged launch, and one sample less
+    (9, [70001, 1, 65536, 90003]),                 # ragged tiles of several jobs (not a multiple of eight)
+    (17, [262145]), (21, [140003]),                # partly staged windows
+])
+def test_staged_launch_equals_unstaged_slices(policy, modes, sizes):
+    """A launch of 2^17 samples and more (windows staged in LDS, one tile per
+    CU, tiles dealt to the XCDs in runs) equals launches of at most 30,011
+    samples (unstaged) to the bit, job by job."""
+    rng = np.random.default_rng(171 + modes)
+    dt = torch.float64 if policy == ile.ILE_FP64 else torch.float32
+    ot = gu.out_dtype(policy)
+    jobs = [ile.ile_prepare(gu.ctx(), ile.ProblemHost(chirpgen.random_problem(rng, modes, ["H", "L", "V"]),
+                                                      precision=policy)) for _ in sizes]
+    try:
+        ths = [torch.from_numpy(np.ascontiguousarray(chirpgen.prior_samples(rng, n))).to(device="cuda", dtype=dt)
+               for n in sizes]
+        Ls = [torch.empty(n, dtype=ot, device="cuda") for n in sizes]
+        ile.ile_eval_lnL_batch(jobs, sizes, ths, sizes, None, Ls)
+        for job, n, th, L in zip(jobs, sizes, ths, Ls):
+            part = torch.empty(n, dtype=ot, device="cuda")
+            for a in range(0, n, 30011):
+                m = min(30011, n - a)
+                ile.ile_eval_lnL(job, m, th.data_ptr() + a * th.element_size(), n, None,
+                                 part.data_ptr() + a * part.element_size())
+            torch.cuda.synchronize()
+            assert torch.equal(L, part), (n, (L - part).abs().max())
+    finally:
+        for job in jobs:
+            ile.ile_job_release(job)
+
+
 @pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32])
 def test_marginalize_batch_equals_single(policy):
     """The batched estimator and the single-job one use the same tile for a
