@@ -133,6 +133,35 @@ def test_tmarg_batch_equals_single(recs):
             ile.ile_job_release(j)
 
 
+@pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("cfg", [(5, "HL"), (9, "HLV"), (21, "HL")], ids=["hl5", "hlv9", "hl21"])
+def test_tmarg_independent_of_launch(cfg, policy):
+    """The tiles and threads of a launch follow its sample counts; every
+    sample's value is bitwise that of the same sample in a launch of one, of a
+    few or of many samples, and next to other jobs."""
+    rng = np.random.default_rng(74)
+    p = chirpgen.random_problem(rng, cfg[0], list(cfg[1]))
+    job = ile.ile_prepare(gu.ctx(), ile.ProblemHost(p, precision=policy))
+    try:
+        dt = np.float64 if policy == ile.ILE_FP64 else np.float32
+        n = 20001
+        th = np.ascontiguousarray(chirpgen.prior_samples(rng, n).astype(dt))
+        whole = _gpu_tmarg(job, th, policy, 4)[0]
+        cuts = [0, 1, 64, 128, 193, 449, 1473, n]
+        tt = [torch.from_numpy(np.ascontiguousarray(th[:, a:b])).to("cuda") for a, b in zip(cuts, cuts[1:])]
+        outs = [torch.empty(t.shape[1], dtype=gu.out_dtype(policy), device="cuda") for t in tt]
+        ile.ile_eval_lnL_tmarg_batch([job] * len(tt), [t.shape[1] for t in tt], tt, [t.shape[1] for t in tt], None,
+                                     outs, oversample=4)
+        torch.cuda.synchronize()
+        got = torch.cat(outs).double().cpu().numpy()
+        assert np.isfinite(whole).any()
+        assert np.array_equal(got, whole)
+        for a, b in zip(cuts[:-2], cuts[1:-1]):
+            assert np.array_equal(_gpu_tmarg(job, th[:, a:b], policy, 4)[0], whole[a:b])
+    finally:
+        ile.ile_job_release(job)
+
+
 def test_tmarg_rejects():
     rng = np.random.default_rng(73)
     p = chirpgen.random_problem(rng, 5, ["H", "L"])
