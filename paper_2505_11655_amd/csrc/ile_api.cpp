@@ -69,12 +69,14 @@ hipError_t launch_eval(int set, int kdet, int policy, bool dm, size_t lds_bytes,
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_tmarg(int set, int kdet, int policy, int R, bool dm, size_t lds_bytes, const EvalJob *d_jobs,
-                        const Tile *d_tiles, int n_tiles, int block, hipStream_t st) {
-#define ILE_TM(S)                                                                                             \
-    if (set == S) {                                                                                           \
-        if (policy == 0) return launch_tmarg_sp<S, 0>(kdet, R, dm, lds_bytes, d_jobs, d_tiles, n_tiles, block, st); \
-        if (policy == 1) return launch_tmarg_sp<S, 1>(kdet, R, dm, lds_bytes, d_jobs, d_tiles, n_tiles, block, st); \
+hipError_t launch_tmarg(int set, int kdet, int policy, int R, bool dm, size_t lds_bytes, int sr, int gs,
+                        const EvalJob *d_jobs, const Tile *d_tiles, int n_tiles, int block, hipStream_t st) {
+#define ILE_TM(S)                                                                                              \
+    if (set == S) {                                                                                            \
+        if (policy == 0)                                                                                       \
+            return launch_tmarg_sp<S, 0>(kdet, R, dm, lds_bytes, sr, gs, d_jobs, d_tiles, n_tiles, block, st); \
+        if (policy == 1)                                                                                       \
+            return launch_tmarg_sp<S, 1>(kdet, R, dm, lds_bytes, sr, gs, d_jobs, d_tiles, n_tiles, block, st); \
     }
     ILE_TM(0)
     ILE_TM(1)
@@ -92,8 +94,8 @@ size_t out_size(int policy) { return policy == kFP32 ? sizeof(float) : sizeof(do
 
 // Detectors of a job read through L1/L2 by the LDS-staged kernel (the same
 // rule as the kernels' instantiation), the bytes of the other detectors'
-// windows that it stages, and whether such a kernel exists for the job and
-// its staged part fits the device.
+// windows that it stages, and whether such a pointwise kernel exists for the
+// job and its staged part fits the device.
 static int job_global_dets(const ile_job *job, bool tmarg) {
     return tmarg ? tmarg_global_dets(job->set, job->kp, job->policy)
                  : lds_global_dets(job->set, job->kp, job->policy);
@@ -103,10 +105,8 @@ size_t job_window_bytes(const ile_job *job, bool tmarg) {
     const size_t series = job->policy == kMixed ? (size_t)job->kp * job->n_time * sizeof(double) : 0;
     return (size_t)std::max(staged, 0) * job->n_time * kSets[job->set].n * 2 * creal_size(job->policy) + series;
 }
-bool job_lds_ok(const ile_job *job, bool tmarg) {
-    const bool compiled = tmarg ? tmarg_lds_compiled(job->set, job->kp, job->policy)
-                                : lnl_lds_compiled(job->set, job->kp, job->policy);
-    return compiled && job_window_bytes(job, tmarg) <= eval_lds_limit();
+bool job_lds_ok(const ile_job *job) {
+    return lnl_lds_compiled(job->set, job->kp, job->policy) && job_window_bytes(job, false) <= eval_lds_limit();
 }
 
 // Samples per block of an LDS-staged launch: every block stages its job's
@@ -848,53 +848,109 @@ extern "C" ile_status ile_eval_lnL_tmarg_batch(ile_job *const *jobs, int32_t n_j
 
 namespace ile {
 
-// Samples per block of a time-marginalised launch, at most `most`: the smallest
-// tile whose tiles fill the 256 CUs in the fewest rounds, and as many threads
-// (at most *block, which is set to them) as its iterations share it evenly.
-// With fixed tiles 4 x 8,191 FP64 samples ran on 32 CUs (1.33 ms) and
-// 16 x 16,384 FP32 samples on 128 (0.77 ms).
-static int64_t tmarg_tile(const std::vector<int64_t> &n, int64_t most, int *block) {
+// Samples per block of a time-marginalised launch, a multiple of `unit` and at
+// most `most`: the smallest tile whose tiles fill the 256 CUs in the fewest
+// rounds.  (With fixed tiles 4 x 8,191 FP64 samples ran on 32 CUs and
+// 16 x 16,384 FP32 samples on 128: 1.33 and 0.77 ms against 0.38 and 0.39 with
+// a sample per lane.)
+static int64_t tmarg_tile(const std::vector<int64_t> &n, int64_t unit, int64_t most) {
     constexpr int64_t kCus = 256;
     int64_t total = 0;
     for (int64_t v : n) total += v;
     const int64_t rounds = std::max<int64_t>(1, (total + kCus * most - 1) / (kCus * most));
-    int64_t t = std::max<int64_t>(64, (total / (kCus * rounds) + 63) / 64 * 64);
-    for (; t < most; t += 64) {
+    int64_t t = std::max<int64_t>(unit, (total / (kCus * rounds) + unit - 1) / unit * unit);
+    for (; t < most; t += unit) {
         int64_t tiles = 0;
         for (int64_t v : n) tiles += (v + t - 1) / t;
         if (tiles <= kCus * rounds || tiles == (int64_t)n.size()) break;
     }
-    t = std::min(t, most);
-    const int64_t iters = (t + *block - 1) / *block;
-    *block = (int)((t + iters - 1) / iters + 63) / 64 * 64;
-    return t;
+    return std::min(t, most);
 }
 
-// Time-marginalised evaluation: jobs grouped by compiled kernel, the window
-// staged in LDS whenever it fits (each sample does hundreds of nodes of work).
+// A job's passes by rounds of sixteen samples: the longest pass (in 64-step
+// chunks) whose window times fit the LDS beside sixteen samples' coefficients; the
+// times of a pass are its steps, the stencil and the samples' spread (twice
+// the light travel time between the detector and the geocentre), and the
+// window at most.  0 chunks: none fits (sample rates above 20 kHz or so).
+static void tmarg_pass(const ile_job *j, int R, int half, int *chunks, int *rows) {
+    const EvalJob &e = j->ej;
+    double r = 0.0;
+    for (int k = 0; k < j->kp; k++)
+        r = std::max(r, std::sqrt(e.xc[k][0] * e.xc[k][0] + e.xc[k][1] * e.xc[k][1] + e.xc[k][2] * e.xc[k][2]));
+    const double spread = std::ceil(2.0 * r * e.inv_dt) + 2.0;
+    const int64_t steps = (int64_t)half / R + (half + R - 1) / R + 1;
+    *chunks = 0;
+    for (int c = (int)std::min<int64_t>(kTmChunks, (steps + 63) / 64); c > 0 && spread < 1e6; c--) {
+        const int64_t need = std::min<int64_t>(std::min<int64_t>(64 * c, steps) + 4 + (int64_t)spread, e.n_time + 2);
+        *rows = (int)std::max<int64_t>(need, 5);
+        if (tm_lds_bytes(j->set, j->kp, R, kTmCols, tm_stride(*rows)) <= eval_lds_limit()) {
+            *chunks = c;
+            return;
+        }
+    }
+    *rows = 0;
+}
+
+static void xcd_order(std::vector<Tile> &tiles);
+
+// Time-marginalised evaluation: jobs grouped by compiled kernel.
 ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R, hipStream_t st) {
     if (R != 1 && R != 4) return set_err(ILE_E_INVALID, "oversample must be 1 or 4");
-    std::map<std::tuple<int, int, int, int>, std::vector<int>> groups;
+    struct Node {
+        int half = 0, chunks = 0, rows = 0;
+        double lnw = 0.0;
+    };
+    std::vector<Node> nodes(items.size());
+    std::map<std::tuple<int, int, int, int, int>, std::vector<int>> groups;
     for (size_t i = 0; i < items.size(); i++) {
         const ile_job *j = items[i].job;
         if (j->policy == kMixed) return set_err(ILE_E_INVALID, "time marginalisation supports FP32 and FP64 jobs");
         if (items[i].n == 0) continue;
-        groups[std::make_tuple(j->set, j->kp, j->policy, j->dist_marg ? 1 : 0)].push_back((int)i);
+        const double dt = 1.0 / j->ej.inv_dt, tw = j->pr.t_window;
+        const double half = std::floor(R * tw / dt + 1e-9);
+        if (!(half >= 0 && half < 1e6)) return set_err(ILE_E_INVALID, "time window too long for marginalisation");
+        Node &d = nodes[i];
+        d.half = (int)half;
+        d.lnw = std::log(dt / (R * 2.0 * tw));
+        if (tm_rounds(j->set, j->policy, R, j->dist_marg)) tmarg_pass(j, R, d.half, &d.chunks, &d.rows);
+        groups[std::make_tuple(j->set, j->kp, j->policy, j->dist_marg ? 1 : 0, d.chunks > 0 ? 1 : 0)].push_back((int)i);
     }
     std::lock_guard<std::mutex> lk(ctx->batch_mu);
     for (auto &g : groups) {
         const auto &idx = g.second;
-        size_t win = 0;
-        bool lds = true;
-        for (int i : idx) {
-            win = std::max(win, job_window_bytes(items[i].job, true));
-            lds = lds && job_lds_ok(items[i].job, true);
-        }
-        const int policy = std::get<2>(g.first);
+        const int set = std::get<0>(g.first), kp = std::get<1>(g.first), policy = std::get<2>(g.first);
+        const bool dm = std::get<3>(g.first) != 0, rounds = std::get<4>(g.first) != 0;
         std::vector<int64_t> ns;
-        for (int i : idx) ns.push_back(items[i].n);
-        int block = tmarg_block_threads(policy);
-        const int64_t tile = tmarg_tile(ns, lds ? 4 * block : block, &block);
+        int rows_max = 0;
+        size_t win = 0;
+        for (int i : idx) {
+            ns.push_back(items[i].n);
+            rows_max = std::max(rows_max, nodes[i].rows);
+            win = std::max(win, job_window_bytes(items[i].job, true));
+        }
+        const bool staged =
+            !rounds && tmarg_lds_compiled(set, kp, policy, R, dm) && win <= eval_lds_limit();
+        // A sample per lane: the window staged in LDS whenever it fits (each
+        // sample does hundreds of nodes of work).  By rounds: one block per CU,
+        // with as many samples set up at a time as fit.
+        int sr = 0, gs = 0, block = tmarg_block_threads(policy);
+        size_t lds = staged ? win : 0;
+        int64_t unit = 64, most = staged ? 4 * block : block;
+        if (rounds) {
+            block = kTmWaves * 64;
+            gs = tm_stride(rows_max);
+            for (sr = kTmSetup; sr > kTmCols; sr /= 2)
+                if (tm_lds_bytes(set, kp, R, sr, gs) <= eval_lds_limit()) break;
+            lds = tm_lds_bytes(set, kp, R, sr, gs);
+            unit = kTmCols;
+            most = 1024;
+        }
+        const int64_t tile = tmarg_tile(ns, unit, most);
+        if (!rounds) {
+            // as many threads as the tile's iterations share evenly
+            const int64_t iters = (tile + block - 1) / block;
+            block = (int)((tile + iters - 1) / iters + 63) / 64 * 64;
+        }
         std::vector<EvalJob> ej;
         std::vector<Tile> tiles;
         for (int i : idx) {
@@ -906,24 +962,22 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
             e.lnL = b.lnL;
             e.lw = b.lw;
             e.n = b.n;
-            const double dt = 1.0 / e.inv_dt, tw = b.job->pr.t_window;
-            const double half = std::floor(R * tw / dt + 1e-9);
-            if (!(half >= 0 && half < 1e6)) return set_err(ILE_E_INVALID, "time window too long for marginalisation");
-            e.tm_half = (int)half;
-            e.tm_lnw = std::log(dt / (R * 2.0 * tw));
+            e.tm_half = nodes[i].half;
+            e.tm_chunks = nodes[i].chunks;
+            e.tm_lnw = nodes[i].lnw;
             const int jid = (int)ej.size();
             ej.push_back(e);
             for (int64_t t0 = 0; t0 < b.n; t0 += tile) tiles.push_back(Tile{jid, 0, t0, std::min(t0 + tile, b.n)});
         }
         if (tiles.size() > (size_t)INT32_MAX) return set_err(ILE_E_INVALID, "too many samples for one launch");
+        xcd_order(tiles);
         void *dj = nullptr, *dt = nullptr;
         int slot = -1;
         ile_status s = batch_upload(ctx, ej.data(), ej.size() * sizeof(EvalJob), tiles.data(),
                                     tiles.size() * sizeof(Tile), &dj, &dt, &slot, st);
         if (s != ILE_OK) return s;
-        hipError_t e = launch_tmarg(std::get<0>(g.first), std::get<1>(g.first), policy, R, std::get<3>(g.first) != 0,
-                                    lds ? win : 0,
-                                    (const EvalJob *)dj, (const Tile *)dt, (int)tiles.size(), block, st);
+        hipError_t e = launch_tmarg(set, kp, policy, R, dm, lds, sr, gs, (const EvalJob *)dj,
+                                    (const Tile *)dt, (int)tiles.size(), block, st);
         if (e != hipSuccess) return dev_fail(ctx, e, "time-marginalised eval launch");
         if ((s = batch_done(ctx, slot, st)) != ILE_OK) return s;
     }
@@ -965,7 +1019,7 @@ ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStre
             total += items[i].n;
             const ile_job *j = items[i].job;
             win = std::max(win, job_window_bytes(j, false));
-            lds_ok = lds_ok && job_lds_ok(j, false);
+            lds_ok = lds_ok && job_lds_ok(j);
             ns.push_back(items[i].n);
         }
         // LDS-staged from 512 samples per CU up (2^17 samples, HLV 9 modes: FP32

@@ -59,8 +59,9 @@ constexpr int lds_global_dets(int set, int kp, int policy) {
         if ((kp - g) * per + fixed <= 163840L) return g;
     return kp;
 }
-// The time-marginalised kernel always reads at least the first detector
-// through L1/L2 (its per-lane row reads exceed the LDS bandwidth otherwise).
+// The time-marginalised kernel with a sample per lane always reads at least the
+// first detector through L1/L2 (its per-lane row reads exceed the LDS bandwidth
+// otherwise).
 constexpr int tmarg_global_dets(int set, int kp, int policy) {
     const int g = lds_global_dets(set, kp, policy);
     return g > 1 ? g : 1;
@@ -68,15 +69,37 @@ constexpr int tmarg_global_dets(int set, int kp, int policy) {
 // Whether an LDS-staged variant is compiled: for the pointwise kernel wherever
 // one detector's window fits, except the 21-mode set of the FP32 +
 // FP64-cancellation policy (one wave per SIMD beside its window: 12 x 300,007
-// samples, three detectors, 1.67 ms against 1.12 unstaged); for the time-marginalised kernel only up to the
-// 9-mode set in FP64 (beyond it the staged variant runs out of scalar
-// registers and gains nothing over L1/L2).
+// samples, three detectors, 1.67 ms against 1.12 unstaged); for the
+// time-marginalised kernel with a sample per lane where that is the kernel
+// (FP64 takes its samples by rounds of sixteen, except with the 5-mode set and
+// one node per step).
+constexpr bool tm_rounds(int set, int policy, int R, bool dm) {
+    return policy == kFP64 && !(set == 0 && R == 1 && !dm);
+}
 constexpr bool lnl_lds_compiled(int set, int kp, int policy) {
     return lds_global_dets(set, kp, policy) < kp && !(policy == kMixed && set == 3);
 }
-constexpr bool tmarg_lds_compiled(int set, int kp, int policy) {
-    return tmarg_global_dets(set, kp, policy) < kp && (set <= 1 || policy == kFP32);
+constexpr bool tmarg_lds_compiled(int set, int kp, int policy, int R, bool dm) {
+    return tmarg_global_dets(set, kp, policy) < kp && !tm_rounds(set, policy, R, dm);
 }
+// FP64 time-marginalised kernel by rounds of sixteen samples: waves of a
+// block, samples of a round, 64-step chunks of a pass at most, samples set up
+// at a time at most (a wave per detector and 64 of them), values after G that
+// its reads may reach, and the LDS of a block that sets up sr samples and holds
+// gs values of G per sample.
+constexpr int kTmWaves = 8;
+constexpr int kTmCols = 16;
+constexpr int kTmChunks = 4;
+constexpr int kTmSetup = 128;
+constexpr int kTmPad = 64 * kTmChunks + 8;
+constexpr size_t tm_lds_bytes(int set, int kp, int R, int sr, int gs) {
+    return 8 * ((size_t)2 * kTmSetup + (size_t)kTmCols * kp * 5 * R + (size_t)(2 * kp + 1) * kTmSetup) +
+           4 * ((size_t)kp * kTmSetup + (size_t)kp * (kTmSetup / kTmCols) * 2 + (size_t)kTmCols * 2 * R) +
+           8 * ((size_t)(kp * 2 * kSets[set].n + 1) * sr + (size_t)kTmCols * gs + kTmPad);
+}
+// Values of G per sample for `rows` window times: whole tiles of sixteen, and
+// a stride that spreads the columns of a tile over the LDS banks.
+constexpr int tm_stride(int rows) { return (rows + 15) / 16 * 16 + 4; }
 
 constexpr int set_lmax(int s) {
     int L = 0;
@@ -235,6 +258,7 @@ struct EvalJob {
     float gmstf, tau0f, inv_dtf, d_reff;
     int n_time;
     int tm_half;          // time-marginalised launches: nodes j = -tm_half..tm_half
+    int tm_chunks;        // 64-step chunks per pass (FP64, rounds of sixteen samples)
     const void *theta;
     int64_t ld;
     const void *lnpmps;

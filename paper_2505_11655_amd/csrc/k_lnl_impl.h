@@ -291,16 +291,17 @@ struct LnlKernel {
     // The quadratic form T2 from the pair tables (read through the scalar cache).
     // CHAIN: the phase rotations of the pair groups as explicit FMA chains
     // (two instructions where acc + (x y - z w) costs three); off for the
-    // time-marginalised kernel, whose register budget the chained form
-    // exceeds (it then spills).
+    // time-marginalised kernel with a sample per lane, whose register budget
+    // the chained form exceeds (it then spills).
+    // ND: the terms of ND detectors, Ut and Vt pointing at the first one's.
     typedef __attribute__((address_space(4))) const cpx<TA> ccpx;
-    template <bool CHAIN = true>
-    __device__ __forceinline__ static TA quad_T2(const TG (&Fr)[K], const TG (&Fi)[K], const TG (&y)[NM],
+    template <bool CHAIN = true, int ND = K>
+    __device__ __forceinline__ static TA quad_T2(const TG (&Fr)[ND], const TG (&Fi)[ND], const TG (&y)[NM],
                                                  const TE (&Er)[NE], const TE (&Ei)[NE], ccpx *Ut, ccpx *Vt) {
         // ---- T2 = sum_k |F_k|^2 Y^+ U_k Y + Re(F_k^2 Y^T V_k Y)
-        TA uk[K], vr[K], vi[K];
+        TA uk[ND], vr[ND], vi[ND];
 #pragma unroll
-        for (int k = 0; k < K; k++) {
+        for (int k = 0; k < ND; k++) {
             uk[k] = (TA)0;
             vr[k] = (TA)0;
             vi[k] = (TA)0;
@@ -309,9 +310,9 @@ struct LnlKernel {
         static_for<0, NE>([&](auto G_) {
             constexpr int g = decltype(G_)::value;
             fence();
-            TA Ar[K], Ai[K];
+            TA Ar[ND], Ai[ND];
 #pragma unroll
-            for (int k = 0; k < K; k++) {
+            for (int k = 0; k < ND; k++) {
                 Ar[k] = (TA)0;
                 Ai[k] = (TA)0;
             }
@@ -320,13 +321,13 @@ struct LnlKernel {
                 constexpr int p = pt.u_pair[j];
                 const TA py = (TA)y[pt.a[p]] * (TA)y[pt.b[p]];
 #pragma unroll
-                for (int k = 0; k < K; k++) {
+                for (int k = 0; k < ND; k++) {
                     Ar[k] += py * Ut[j * K + k].re;
                     if constexpr (g > 0) Ai[k] += py * Ut[j * K + k].im;
                 }
             });
 #pragma unroll
-            for (int k = 0; k < K; k++) {
+            for (int k = 0; k < ND; k++) {
                 if constexpr (g == 0) {
                     uk[k] += Ar[k];
                 } else if constexpr (CHAIN) {
@@ -351,9 +352,9 @@ struct LnlKernel {
             fence();
             constexpr int sm = g - 2 * LM;
             if constexpr (pt.v_start[g + 1] > pt.v_start[g]) {
-                TA Br[K], Bi[K];
+                TA Br[ND], Bi[ND];
 #pragma unroll
-                for (int k = 0; k < K; k++) {
+                for (int k = 0; k < ND; k++) {
                     Br[k] = (TA)0;
                     Bi[k] = (TA)0;
                 }
@@ -362,7 +363,7 @@ struct LnlKernel {
                     constexpr int p = pt.v_pair[j];
                     const TA py = (TA)yv[pt.a[p]] * (TA)yv[pt.b[p]];
 #pragma unroll
-                    for (int k = 0; k < K; k++) {
+                    for (int k = 0; k < ND; k++) {
                         Br[k] += py * Vt[j * K + k].re;
                         Bi[k] += py * Vt[j * K + k].im;
                     }
@@ -371,7 +372,7 @@ struct LnlKernel {
                 const TA er = (TA)Er[sm < 0 ? -sm : sm];
                 const TA ei = (sm < 0) ? (TA)Ei[-sm] : -(TA)Ei[sm];
 #pragma unroll
-                for (int k = 0; k < K; k++) {
+                for (int k = 0; k < ND; k++) {
                     if constexpr (CHAIN) {
                         vr[k] = fma(er, Br[k], vr[k]);
                         vr[k] = fma(-ei, Bi[k], vr[k]);
@@ -386,7 +387,7 @@ struct LnlKernel {
         });
         TA T2 = (TA)0;
 #pragma unroll
-        for (int k = 0; k < K; k++) {
+        for (int k = 0; k < ND; k++) {
             const TA fr = (TA)Fr[k], fi = (TA)Fi[k];
             T2 += (fr * fr + fi * fi) * uk[k] + (fr * fr - fi * fi) * vr[k] - (TA)2 * fr * fi * vi[k];
         }

@@ -162,6 +162,57 @@ def test_tmarg_independent_of_launch(cfg, policy):
         ile.ile_job_release(job)
 
 
+@pytest.mark.parametrize("R", [1, 4])
+@pytest.mark.parametrize("dm", [False, True], ids=["distance", "dist_marg"])
+@pytest.mark.parametrize("rate,t_window", [(1, 0.0), (1, 0.004), (1, 0.0312), (1, 0.0495), (4, 0.03), (6, 0.02),
+                                           (8, 0.01)])
+def test_tmarg_fp64_passes(orc, rate, t_window, dm, R):
+    """FP64 by rounds of sixteen samples at the edges of its passes: one node,
+    a part of a 64-step chunk, one full pass, two passes, the window cut to 4
+    chunks and fewer (sample rates of 16 and 24 kHz) and the kernel with a
+    sample per lane above (32 kHz).  Every value against the pointwise oracle at
+    the nodes; with the distance integrated, against a launch of single nodes."""
+    rng = np.random.default_rng(75)
+    n_modes, dets = (9, ["H", "L", "V"]) if rate == 1 else (5, ["H", "L"])
+    p = chirpgen.random_problem(rng, n_modes, dets)
+    if rate > 1:
+        n_time = p.Q.shape[2] * rate
+        p.Q = (rng.normal(size=(2, 5, n_time)) + 1j * rng.normal(size=(2, 5, n_time))) * 5.0
+        p.dt = p.dt / rate
+    p.t_window = t_window if t_window > 0 else p.dt / 8
+    n = 37
+    th = np.ascontiguousarray(chirpgen.prior_samples(rng, n))
+    th[3, 5], th[4, 6], th[1, 7], th[0, 8] = -1.0, 1.25, np.nan, np.inf
+    th[3, 9] = np.inf
+    job = ile.ile_prepare(gu.ctx(), ile.ProblemHost(p, precision=ile.ILE_FP64, dist_marg=dm))
+    try:
+        L, _ = _gpu_tmarg(job, th, ile.ILE_FP64, R)
+        if dm:
+            tj, lnw = orc.tmarg_grid(p, R)
+            big = np.repeat(th, len(tj), axis=1)
+            big[2] = np.tile(tj, n)
+            t = torch.from_numpy(np.ascontiguousarray(big)).to("cuda")
+            out = torch.empty(big.shape[1], dtype=torch.float64, device="cuda")
+            ile.ile_eval_lnL(job, big.shape[1], t, big.shape[1], None, out, None)
+            torch.cuda.synchronize()
+            node = out.cpu().numpy().reshape(n, len(tj))
+            m = node.max(axis=1)
+            ref = np.full(n, -np.inf)
+            f = np.isfinite(m)
+            ref[f] = m[f] + np.log(np.exp(node[f] - m[f, None]).sum(axis=1)) + lnw
+        else:
+            ref = orc.lnL_tmarg(p, th, oversample=R)
+    finally:
+        ile.ile_job_release(job)
+    bad = [5, 6, 7, 8]
+    assert np.all(np.isneginf(L[bad]))
+    keep = [i for i in range(n) if i not in bad]
+    fin = np.isfinite(ref[keep])
+    assert fin.any()
+    assert np.array_equal(fin, np.isfinite(L[keep]))
+    assert np.allclose(L[keep][fin], ref[keep][fin], rtol=1e-9, atol=1e-9)
+
+
 def test_tmarg_rejects():
     rng = np.random.default_rng(73)
     p = chirpgen.random_problem(rng, 5, ["H", "L"])
