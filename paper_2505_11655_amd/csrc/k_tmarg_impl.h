@@ -20,6 +20,8 @@
 // set up once per sample and each node interpolates along a only (FP64).
 #pragma once
 
+#include <cfloat>
+
 #include "k_lnl_impl.h"
 
 namespace ile {
@@ -45,6 +47,18 @@ struct TmargKernel {
     // modes 33.8 -> 25.5 ms, two of three detectors through L1/L2 39.5 ms;
     // HL 5 modes 16.0 -> 14.5 ms).  Only the other detectors are staged.
     static constexpr int kGlobalDets = LDS ? tmarg_global_dets(S, K, POL) : K;
+
+    typedef __attribute__((address_space(1))) const cpx<TA> gcpx;
+    // FP32: exponents in units of ln 2, so that e^{s T1 - m} is one FMA and
+    // v_exp_f32; the origin m is the same FP32 number in the sum and in the
+    // result, so its rounding cancels.  It follows the maximum only in strides
+    // of kStride (a new origin costs an exponential and an FP64 product, and
+    // every lane rises to its maximum through many), which keeps an exponent's
+    // rounding below 2^-21.  Masks only at the steps where a lane of the wave
+    // has a node outside.  Bound by the vector unit (203 instructions per
+    // step); 16 x 16,384 samples, HLV 9 modes, R = 4: 391 to 365 us.
+    static constexpr bool kExp2 = sizeof(TV) == 4;
+    static constexpr float kStride = 8.0f;
 
     __device__ __forceinline__ static TA expT(TA x) {
         if constexpr (sizeof(TA) == 4)
@@ -148,6 +162,30 @@ struct TmargKernel {
                     qmax[r] = min(qmax[r], hi);
                 }
             }
+            // nodes j = R q + r in [-jh, jh], and the steps at which every lane of
+            // the wave has all its nodes
+            int in_lo = INT32_MIN, in_hi = INT32_MAX;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                qmin[r] = max(qmin[r], -((jh + r) / R));
+                qmax[r] = min(qmax[r], jh >= r ? (jh - r) / R : -1 - (r - jh - 1) / R);
+                in_lo = max(in_lo, qmin[r]);
+                in_hi = min(in_hi, qmax[r]);
+            }
+            // s in the units of the exponents
+            TV se = (TV)s;
+            if constexpr (kExp2) {
+                se = (TV)((double)s * 1.4426950408889634074);
+                if (!(se > (TV)0)) in_lo = INT32_MAX;   // D infinite: every step as one at an edge
+                // (lanes past the last sample read as 0, which can only narrow the range)
+#pragma unroll
+                for (int m = 1; m < 64; m <<= 1) {
+                    in_lo = max(in_lo, __shfl_xor(in_lo, m));
+                    in_hi = min(in_hi, __shfl_xor(in_hi, m));
+                }
+                in_lo = __builtin_amdgcn_readfirstlane(in_lo);
+                in_hi = __builtin_amdgcn_readfirstlane(in_hi);
+            }
             // window G_k(i0 + q - 1 + t), t = 0..4: each step appends the
             // newest sample; the four steps before q_lo only fill the window
             // (their nodes lie below -tm_half and are masked)
@@ -176,13 +214,21 @@ struct TmargKernel {
                     for (int kk = 0; kk < kGroup; kk++) {
                         const int k = k0 + kk;
                         const int ic = min(max(i0[k] + q + 3, 0), T - 1);
-                        const cpx<TA> *qr = (k < kGlobalDets ? Qg + (size_t)k * T * NM
-                                                             : smem + (size_t)(k - kGlobalDets) * T * NM) +
-                                            (size_t)ic * NM;
-                        static_for<0, NM>([&](auto A_) {
-                            constexpr int a = decltype(A_)::value;
-                            qv[kk][a] = qr[a];
-                        });
+                        // (a pointer that may be either would make both loads flat ones)
+                        if (k < kGlobalDets) {
+                            gcpx *qr = (gcpx *)Qg + ((size_t)k * T + ic) * NM;
+                            static_for<0, NM>([&](auto A_) {
+                                constexpr int a = decltype(A_)::value;
+                                qv[kk][a].re = qr[a].re;
+                                qv[kk][a].im = qr[a].im;
+                            });
+                        } else {
+                            const cpx<TA> *qr = smem + ((size_t)(k - kGlobalDets) * T + ic) * NM;
+                            static_for<0, NM>([&](auto A_) {
+                                constexpr int a = decltype(A_)::value;
+                                qv[kk][a] = qr[a];
+                            });
+                        }
                     }
 #pragma unroll
                     for (int kk = 0; kk < kGroup; kk++) {
@@ -198,39 +244,76 @@ struct TmargKernel {
                         G[k][4] = g;
                     }
                 }
-                TV x[R];
-                TV cmax = (TV)-INFINITY;
+                if constexpr (kExp2) {
+                    TV t1[R];
+                    TV tm = -FLT_MAX;
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    const int j = R * q + r;
-                    const bool valid = j >= -jh && j <= jh && q >= qmin[r] && q <= qmax[r];
-                    TA t1 = (TA)0;
+                    for (int r = 0; r < R; r++) {
+                        TA v = (TA)0;
 #pragma unroll
-                    for (int k = 0; k < K; k++)
+                        for (int k = 0; k < K; k++)
 #pragma unroll
-                        for (int t = 0; t < 5; t++) t1 = fma(w5[k][r][t], G[k][t], t1);
-                    if constexpr (DM)
-                        x[r] = valid ? dist_at(J.dt, drow, (double)t1) : -INFINITY;
-                    else
-                        x[r] = valid ? s * t1 : (TA)-INFINITY;
-                    cmax = fmax(cmax, x[r]);
+                            for (int t = 0; t < 5; t++) v = fma(w5[k][r][t], G[k][t], v);
+                        // a NaN or -inf counts as no node: its exponential is 0
+                        t1[r] = fmax(v, -FLT_MAX);
+                    }
+                    const bool edge = q < in_lo || q > in_hi;   // (the same for the wave)
+                    if (edge) {
+#pragma unroll
+                        for (int r = 0; r < R; r++)
+                            t1[r] = q >= qmin[r] && q <= qmax[r] ? t1[r] : -FLT_MAX;
+                    }
+#pragma unroll
+                    for (int r = 0; r < R; r++) tm = fmax(tm, t1[r]);
+                    const TV xm = se * tm;
+                    if (xm > mx + kStride && tm > -FLT_MAX) {
+                        sum = (mx > -INFINITY) ? sum * (double)__builtin_amdgcn_exp2f(mx - xm) : 0.0;
+                        mx = xm;
+                    }
+                    TV part = (TV)0;
+                    if (edge) {
+#pragma unroll
+                        for (int r = 0; r < R; r++)
+                            part += t1[r] > -FLT_MAX ? __builtin_amdgcn_exp2f(fma(se, t1[r], -mx)) : (TV)0;
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < R; r++) part += __builtin_amdgcn_exp2f(fma(se, t1[r], -mx));
+                    }
+                    sum += (double)part;
+                } else {
+                    TV x[R];
+                    TV cmax = (TV)-INFINITY;
+#pragma unroll
+                    for (int r = 0; r < R; r++) {
+                        const bool valid = q >= qmin[r] && q <= qmax[r];
+                        TA t1 = (TA)0;
+#pragma unroll
+                        for (int k = 0; k < K; k++)
+#pragma unroll
+                            for (int t = 0; t < 5; t++) t1 = fma(w5[k][r][t], G[k][t], t1);
+                        if constexpr (DM)
+                            x[r] = valid ? dist_at(J.dt, drow, (double)t1) : -INFINITY;
+                        else
+                            x[r] = valid ? s * t1 : (TA)-INFINITY;
+                        cmax = fmax(cmax, x[r]);
+                    }
+                    if (cmax > mx) {
+                        if constexpr (DM)
+                            sum = (mx > -INFINITY) ? sum * exp(mx - cmax) : 0.0;
+                        else
+                            sum = (mx > (TA)-INFINITY) ? sum * (double)expT(mx - cmax) : 0.0;
+                        mx = cmax;
+                    }
+                    TV part = (TV)0;
+#pragma unroll
+                    for (int r = 0; r < R; r++) {
+                        if constexpr (DM)
+                            part += (x[r] > -INFINITY) ? exp(x[r] - mx) : 0.0;
+                        else
+                            part += (x[r] > (TA)-INFINITY) ? expT(x[r] - mx) : (TA)0;
+                    }
+                    sum += (double)part;
                 }
-                if (cmax > mx) {
-                    if constexpr (DM)
-                        sum = (mx > -INFINITY) ? sum * exp(mx - cmax) : 0.0;
-                    else
-                        sum = (mx > (TA)-INFINITY) ? sum * (double)expT(mx - cmax) : 0.0;
-                    mx = cmax;
-                }
-                TV part = (TV)0;
-#pragma unroll
-                for (int r = 0; r < R; r++) {
-                    if constexpr (DM)
-                        part += (x[r] > -INFINITY) ? exp(x[r] - mx) : 0.0;
-                    else
-                        part += (x[r] > (TA)-INFINITY) ? expT(x[r] - mx) : (TA)0;
-                }
-                sum += (double)part;
             }
             if constexpr (!kT2First) {
                 // the table pointers look redefined here, so the scalar loads
@@ -244,7 +327,8 @@ struct TmargKernel {
                 if (ok && mx > -INFINITY) lnLt = (double)mx + log(sum) + J.tm_lnw;
             } else {
                 if (ok && mx > (TA)-INFINITY)
-                    lnLt = (double)mx + log(sum) - (double)(s * s * T2 * (TA)0.25) + J.tm_lnw;
+                    lnLt = (double)mx * (kExp2 ? 0.69314718055994530942 : 1.0) + log(sum) -
+                           (double)(s * s * T2 * (TA)0.25) + J.tm_lnw;
             }
             const TO outv = (TO)lnLt;
             if (outL) outL[i] = outv;

@@ -213,6 +213,35 @@ def test_tmarg_fp64_passes(orc, rate, t_window, dm, R):
     assert np.allclose(L[keep][fin], ref[keep][fin], rtol=1e-9, atol=1e-9)
 
 
+@pytest.mark.parametrize("R", [1, 4])
+@pytest.mark.parametrize("cfg", [(5, "HL"), (9, "HLV"), (17, "HLV")], ids=["hl5", "hlv9", "hlv17"])
+def test_tmarg_fp32_edges(orc, cfg, R):
+    """FP32: nodes outside the window at both ends of the time prior, samples
+    outside the support or with a NaN angle (-inf), D infinite (every node inside
+    weighs 1) and the rest of a ragged wave beside them."""
+    rng = np.random.default_rng(76)
+    p = chirpgen.random_problem(rng, cfg[0], list(cfg[1]))
+    p.Q, p.U, p.V = p.Q * 0.5, p.U * 0.25, p.V * 0.25
+    p.t_window = 0.0495
+    n = 139
+    th = np.ascontiguousarray(chirpgen.prior_samples(rng, n).astype(np.float32))
+    th[3, 64:70] = -3.0
+    th[4, 70:74] = 1.5
+    th[1, 74], th[0, 75] = np.nan, np.inf
+    th[3, 80] = np.inf
+    job = ile.ile_prepare(gu.ctx(), ile.ProblemHost(p, precision=ile.ILE_FP32))
+    try:
+        L, _ = _gpu_tmarg(job, th, ile.ILE_FP32, R)
+    finally:
+        ile.ile_job_release(job)
+    bad = np.arange(64, 76)
+    assert np.all(np.isneginf(L[bad]))
+    keep = np.setdiff1d(np.arange(n), bad)
+    (ok, _, _), ref = _check(orc, p, np.ascontiguousarray(th[:, keep]), L[keep], ile.ILE_FP32, R)
+    assert ok
+    assert np.isfinite(ref).all()
+
+
 def test_tmarg_rejects():
     rng = np.random.default_rng(73)
     p = chirpgen.random_problem(rng, 5, ["H", "L"])
