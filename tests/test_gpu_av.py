@@ -100,6 +100,29 @@ def test_av_draws_and_updates_match_oracle(orc, policy):
         ile.ile_job_release(job)
 
 
+@pytest.mark.parametrize("n", [1, 63, 256, 257, 1025, (1 << 20) + 259])
+@pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32], ids=["fp64", "fp32"])
+def test_av_update_sizes(orc, policy, n):
+    """Two updates at the edges of the blocks: one sample, parts of a wave, a
+    block and a span, and spans of two 256-sample rows; ties across blocks and a
+    last block that is nearly empty."""
+    p, job = _job(policy, seed=94)
+    pr = orc.make_prior(t_window=p.t_window, d_min=p.d_min, d_max=p.d_max)
+    g = orc.av_init()
+    rng = np.random.default_rng(95)
+    npdt = np.float32 if policy == ile.ILE_FP32 else np.float64
+    try:
+        ile.ile_av_reset(job)
+        for rnd, kind in enumerate(["gauss", "ties"]):
+            _, u = orc.draw_av(pr, g, 5, rnd, 0, n)
+            lw = _synthetic_lw(rng, u, kind, npdt)
+            st = ile.ile_av_update(job, 5, rnd, 0, n, torch.from_numpy(lw).to("cuda"), ile.av_opts(n_min_live=100))
+            g, info = orc.av_update(g, u, lw.astype(np.float64), n_min_live=100)
+            _compare_grid(job, g, info, st)
+    finally:
+        ile.ile_job_release(job)
+
+
 def test_av_threshold_edge_cases(orc):
     """No finite weight keeps the grid; a single finite sample; p_thr = 1 and
     n_min_live above n (every finite sample kept); NaN and +/-0 handled as the
