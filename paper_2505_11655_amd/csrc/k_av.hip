@@ -420,7 +420,7 @@ __device__ __forceinline__ int64_t av_span(int64_t n) {
     return (n + (int64_t)kAvThreads * 4096 - 1) / ((int64_t)kAvThreads * 4096) * kAvThreads;
 }
 
-// First samples of every span, a wave per span; the job's last block turns the
+// First samples of every span, a wave at a span; the job's last block turns the
 // counts into offsets (in place), which gives the new number of cells, and makes
 // the new grid the current one.  (The last block's turn costs every block a
 // fence: 2^16 samples in 256 blocks 12 us, in 64 8.)
@@ -431,8 +431,7 @@ __global__ void __launch_bounds__(kAvThreads) k_av_count(const AvJob *__restrict
     const int64_t span = av_span(J.n);
     const int nblk = (int)((J.n + span - 1) / span);
     if (!S.valid || (int)blockIdx.x * kWaves >= nblk) return;
-    const int sp = (int)blockIdx.x * kWaves + (int)(threadIdx.x >> 6);
-    if (sp < nblk) {
+    for (int sp = (int)blockIdx.x * kWaves + (int)(threadIdx.x >> 6); sp < nblk; sp += (int)gridDim.x * kWaves) {
         int cnt = 0;
         const int64_t s1 = (sp + 1) * span;
         for (int64_t s = sp * span + (threadIdx.x & 63); s < s1; s += 256) {
@@ -442,7 +441,8 @@ __global__ void __launch_bounds__(kAvThreads) k_av_count(const AvJob *__restrict
         }
         if ((threadIdx.x & 63) == 0) J.b.bcnt[sp] = (uint32_t)cnt;
     }
-    if (!av_last(S, (unsigned)((nblk + kWaves - 1) / kWaves))) return;
+    const unsigned blocks = (unsigned)((nblk + kWaves - 1) / kWaves);
+    if (!av_last(S, blocks < gridDim.x ? blocks : gridDim.x)) return;
     const int per = (nblk + kAvThreads - 1) / kAvThreads;   // at most 16
     const int lo = threadIdx.x * per;
     uint32_t c[16];
@@ -505,11 +505,16 @@ __global__ void __launch_bounds__(kAvThreads) k_av_compact(const AvJob *__restri
     }
 }
 
-// Draws and insertions are chains of latency (counters, inverse CDFs, set
-// atomics) and take a sample per thread up to 2^20: 2^16 samples 4.7 and 6.8 us,
-// 9.2 and 15 with four.
-int grid_for(int64_t n, int per_thread) {
-    const int64_t g = (n + (int64_t)kAvThreads * per_thread - 1) / ((int64_t)kAvThreads * per_thread);
+// Blocks per job: samples per thread from `least` (few samples, every kernel is
+// a chain of latency: 2^16 samples draw in 4.7 us and insert in 6.8 with one per
+// thread, 9.2 and 15 with four) to `most`, which a launch reaches as it fills
+// the chip (the blocks' merges, fences and shared state then cost more than the
+// chains: 100 jobs served, 2^16 samples a round, 106 ms with up to sixteen,
+// 129 with the least).
+int grid_for(int64_t n, int n_jobs, int least, int most) {
+    const int64_t fill = n * n_jobs / ((int64_t)kAvThreads * 512);
+    const int64_t per = std::max<int64_t>(least, std::min<int64_t>(most, fill));
+    const int64_t g = (n + kAvThreads * per - 1) / (kAvThreads * per);
     return (int)(g < 1 ? 1 : (g > 4096 ? 4096 : g));
 }
 
@@ -519,13 +524,13 @@ hipError_t av_update_t(const AvJob *d, int n_jobs, int64_t nmax, hipStream_t st)
     const unsigned nz = (unsigned)n_jobs;
     uint64_t used = 1024;
     while (used < (uint64_t)2 * (uint64_t)nmax) used <<= 1;
-    hipLaunchKernelGGL(k_av_begin, dim3(grid_for((int64_t)used, 4), 1, nz), dim3(kAvThreads), 0, st, d);
-    hipLaunchKernelGGL(k_av_max<TO>, dim3(grid_for(nmax, 4), 1, nz), dim3(kAvThreads), 0, st, d);
+    hipLaunchKernelGGL(k_av_begin, dim3(grid_for((int64_t)used, n_jobs, 4, 4), 1, nz), dim3(kAvThreads), 0, st, d);
+    hipLaunchKernelGGL(k_av_max<TO>, dim3(grid_for(nmax, n_jobs, 4, 16), 1, nz), dim3(kAvThreads), 0, st, d);
     for (int shift = nbits - 8; shift >= 0; shift -= 8)
-        hipLaunchKernelGGL(k_av_hist<TO>, dim3(grid_for(nmax, 4), 1, nz), dim3(kAvThreads), 0, st, d, shift);
-    hipLaunchKernelGGL(k_av_insert<TO>, dim3(grid_for(nmax, 1), 1, nz), dim3(kAvThreads), 0, st, d);
+        hipLaunchKernelGGL(k_av_hist<TO>, dim3(grid_for(nmax, n_jobs, 4, 16), 1, nz), dim3(kAvThreads), 0, st, d, shift);
+    hipLaunchKernelGGL(k_av_insert<TO>, dim3(grid_for(nmax, n_jobs, 1, 4), 1, nz), dim3(kAvThreads), 0, st, d);
     const int nblk = (int)std::min<int64_t>((nmax + kAvThreads - 1) / kAvThreads, 4096);
-    hipLaunchKernelGGL(k_av_count, dim3((nblk + 3) / 4, 1, nz), dim3(kAvThreads), 0, st, d);
+    hipLaunchKernelGGL(k_av_count, dim3(std::min(grid_for(nmax, n_jobs, 4, 16), (nblk + 3) / 4), 1, nz), dim3(kAvThreads), 0, st, d);
     hipLaunchKernelGGL(k_av_compact, dim3(nblk, 1, nz), dim3(kAvThreads), 0, st, d);
     return hipGetLastError();
 }
@@ -548,7 +553,7 @@ hipError_t launch_av_reset(const AvBufs &b, int d, const int *dims, hipStream_t 
 hipError_t launch_av_draw(int policy, const AvJob *d_jobs, const AvJob *h_jobs, int n_jobs, hipStream_t st) {
     const int64_t nmax = max_n(h_jobs, n_jobs);
     if (n_jobs <= 0 || nmax <= 0) return hipSuccess;
-    const dim3 grid(grid_for(nmax, 1), 1, (unsigned)n_jobs);
+    const dim3 grid(grid_for(nmax, n_jobs, 1, 4), 1, (unsigned)n_jobs);
     if (policy == kFP64)
         hipLaunchKernelGGL(k_av_draw<double>, grid, dim3(kAvThreads), 0, st, d_jobs);
     else
