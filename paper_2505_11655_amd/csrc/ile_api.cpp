@@ -1109,6 +1109,7 @@ ile_status batch_done(ile_ctx *ctx, int slot, hipStream_t st) {
     ile_ctx::Slot &sl = ctx->slots[slot];
     hipError_t e = hipEventRecord(sl.ev, st);
     if (e != hipSuccess) return dev_fail(ctx, e, "slot event");
+    sl.st = st;
     sl.armed = true;
     return ILE_OK;
 }

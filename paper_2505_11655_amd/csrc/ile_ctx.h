@@ -36,6 +36,7 @@ struct ile_ctx {
         void *h = nullptr;
         size_t cap = 0;
         hipEvent_t ev = nullptr;
+        hipStream_t st = nullptr;   // the stream ev was last recorded on
         bool armed = false;
     };
     static constexpr int kSlots = 8;

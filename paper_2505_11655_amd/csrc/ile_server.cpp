@@ -725,6 +725,17 @@ extern "C" void ile_server_destroy(ile_server *s) {
         s->queue.clear();
     }
     s->cv_done.notify_all();
+    {
+        // The context's scratch slots outlive the stream: the work their events
+        // stand for is done, and no one may wait for an event of a stream that
+        // is gone (the next server's first passes would).
+        std::lock_guard<std::mutex> lk(s->ctx->batch_mu);
+        for (auto &sl : s->ctx->slots)
+            if (sl.st == s->stream) {
+                sl.armed = false;
+                sl.st = nullptr;
+            }
+    }
     if (s->up_ev) (void)hipEventDestroy(s->up_ev);
     if (s->up) (void)hipStreamDestroy(s->up);
     (void)hipStreamDestroy(s->stream);
