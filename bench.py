@@ -42,7 +42,7 @@ LNL_BYTES = {"fp32": 40, "fp64": 80}
 # the kernel executes (64 lanes x (add + mul + 2 fma + trans) per wave
 # instruction): 2,437 FP32 + 108 FP64 (sky direction and delays).
 LNL_TRAFFIC = {"fetch_B_per_sample": 32.093, "write_B_per_sample": 8.000, "executed_flop_per_sample": 2545.0,
-               "src_sha256": "75f4e7c04aba3efc98ff70bb4f2cf640c24bf789afdafaafba41f65ef4b4c993"}
+               "src_sha256": "c9bd33a91dfeea330965929b2b792277e7c7a74ab059b71f08d0bd6450880fa8"}
 # algorithmic HBM bytes per sample of the draw (7 theta + ln p - ln p_s
 # written) and estimator (lw read) kernels
 DRAW_BYTES = {"fp32": 32, "fp64": 64}

@@ -340,12 +340,15 @@ struct LnlKernel {
         });
         // The V groups form the pair products again from y as redefined here:
         // kept from the U groups (the same values) they hold P registers
-        // (twice that in FP64) across the whole form and cost the occupancy.
+        // (twice that in FP64) across the whole form and cost the occupancy.  Not
+        // in the unstaged FP32 kernel, whose launches leave a wave or two per SIMD:
+        // there the longer chain costs more (17 modes, 3 x 2^14 samples or so: 44
+        // us against 51).
         TG yv[NM];
 #pragma unroll
         for (int a = 0; a < NM; a++) {
             yv[a] = y[a];
-            if constexpr (MS::P * (sizeof(TA) / 4) > 64) asm volatile("" : "+v"(yv[a]));
+            if constexpr (MS::P * (sizeof(TA) / 4) > 64 && (LDS || sizeof(TA) == 8)) asm volatile("" : "+v"(yv[a]));
         }
         static_for<0, 4 * LM + 1>([&](auto G_) {
             constexpr int g = decltype(G_)::value;
@@ -505,14 +508,16 @@ struct LnlKernel {
 };
 
 // Minimum waves per SIMD asked of the register allocator: those of one
-// LDS-staged block per CU; the unstaged variant reaches at least as many.
-template <int S, int POL>
+// LDS-staged block per CU, which the unstaged FP64 variant reaches as well; two
+// for the unstaged FP32 variant (small launches), one with 21 modes.
+template <int S, int POL, bool LDS>
 constexpr int lnl_min_waves() {
+    if (!LDS && POL == kFP32) return S == 3 ? 1 : 2;
     return lds_block_threads(S, POL) / 256;
 }
 
 template <int S, int K, int POL, bool LDS, bool DM>
-__global__ void __launch_bounds__(LDS ? lds_block_threads(S, POL) : 256, (lnl_min_waves<S, POL>()))
+__global__ void __launch_bounds__(LDS ? lds_block_threads(S, POL) : 256, (lnl_min_waves<S, POL, LDS>()))
     k_lnl(const EvalJob *__restrict__ jobs, const Tile *__restrict__ tiles) {
     extern __shared__ __align__(16) char ile_smem[];
     using TA = typename PolTypes<POL>::TA;
