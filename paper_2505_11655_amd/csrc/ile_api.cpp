@@ -1026,13 +1026,14 @@ ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStre
             lds_ok = lds_ok && job_lds_ok(j);
             ns.push_back(items[i].n);
         }
-        // LDS-staged from 512 samples per CU up (2^17 samples, HLV 9 modes: FP32
-        // 22 against 24 us unstaged, FP64 30 against 39; 2^20: 68 against 104,
-        // 114 against 236).  Below, and where no window fits: about four
-        // 256-thread blocks per CU over the whole batch (small batches would
-        // otherwise leave most CUs idle), 256 to 8192 samples per tile.
-        const int64_t cus = 256;
-        int64_t tile = lds_ok && total >= cus * 512 ? staged_tile(ns) : 0;
+        // LDS-staged from 512 samples per CU up (2^17 samples, HLV 9 modes, FP64: 30
+        // us against 39 unstaged; 2^20: 114 against 236), in FP32 from above that
+        // (2^17, HL 21 modes: 42 against 38; 2^18, HLV 9 modes: 29 against 44).
+        // Below, and where no window fits: about four 256-thread blocks per CU over
+        // the whole batch (small batches would otherwise leave most CUs idle), 256
+        // to 8192 samples per tile.
+        const int64_t cus = 256, least = cus * 512 + (std::get<2>(g.first) == kFP32 ? 1 : 0);
+        int64_t tile = lds_ok && total >= least ? staged_tile(ns) : 0;
         const bool lds = tile > 0;
         if (!lds) {
             tile = (total + 4 * cus - 1) / (4 * cus);
