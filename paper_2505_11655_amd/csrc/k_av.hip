@@ -165,17 +165,19 @@ __global__ void __launch_bounds__(kAvThreads) k_av_begin(const AvJob *__restrict
 }
 
 // True in every thread of the last of a job's `blocks` blocks to get here; what
-// the others wrote before is then visible to agent-scope loads.
+// the others wrote before is then visible to agent-scope loads.  Every thread
+// releases before the barrier: the barrier alone does not wait for the other
+// waves' global atomics and stores, and thread 0's fence covers its own wave's.
 __device__ __forceinline__ bool av_last(AvDev &S, unsigned blocks) {
     __shared__ bool last;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
         last = atomicAdd(&S.done, 1u) == blocks - 1;
         if (last) S.done = 0;   // for the next kernel
-        __threadfence();
     }
     __syncthreads();
+    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     return last;
 }
 template <class T>
