@@ -328,22 +328,35 @@ __device__ void av_pick(const AvJob &J, int shift) {
             S.valid = 1;
         }
     }
+    // the first thread (highest bucket) that reaches the target, found as such:
+    // the masses wrap at 2^64 (more than 2^24 samples at the maximum), and a
+    // lower bucket can then reach the target again behind one that does not
+    __shared__ unsigned long long sh_hit[2][kAvThreads / 64];
+    unsigned long long above_c[2], above_m[2], prefix[2];
 #pragma unroll
     for (int c = 0; c < 2; c++) {
-        // the first thread (highest bucket) that reaches the target
-        const unsigned long long above_c = S.above_cnt[c], above_m = S.above_mass[c];
-        const bool hit = c == 0 ? above_m + suf_m[0] >= target0 : above_c + suf_c[1] >= target1;
-        const bool before = c == 0 ? above_m + suf_m[0] - mm[0] >= target0 : above_c + suf_c[1] - cc[1] >= target1;
-        const unsigned long long prefix = S.prefix[c];
-        __syncthreads();   // every thread has read the chain's state
-        if (hit && (t == 0 || !before)) {
-            const unsigned long long p = prefix | ((unsigned long long)d << shift);
+        above_c[c] = S.above_cnt[c];
+        above_m[c] = S.above_mass[c];
+        prefix[c] = S.prefix[c];
+        const bool hit = c == 0 ? above_m[0] + suf_m[0] >= target0 : above_c[1] + suf_c[1] >= target1;
+        const unsigned long long mask = __ballot(hit);
+        if ((t & 63) == 0) sh_hit[c][t >> 6] = mask;
+    }
+    __syncthreads();   // (and every thread has read the chains' state)
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+        int first = kAvThreads;
+#pragma unroll
+        for (int w = kAvThreads / 64 - 1; w >= 0; w--)
+            if (sh_hit[c][w]) first = 64 * w + __ffsll((long long)sh_hit[c][w]) - 1;
+        if (t == first) {
+            const unsigned long long p = prefix[c] | ((unsigned long long)d << shift);
             S.last_cnt[c] = cc[c];
-            S.above_cnt[c] = above_c + suf_c[c] - cc[c];
-            S.above_mass[c] = above_m + suf_m[c] - mm[c];
+            S.above_cnt[c] = above_c[c] + suf_c[c] - cc[c];
+            S.above_mass[c] = above_m[c] + suf_m[c] - mm[c];
             S.prefix[c] = p;
             sh_prefix[c] = p;
-            sh_count[c] = above_c + suf_c[c];
+            sh_count[c] = above_c[c] + suf_c[c];
         }
     }
     __syncthreads();

@@ -123,6 +123,26 @@ def test_av_update_sizes(orc, policy, n):
         ile.ile_job_release(job)
 
 
+def test_av_threshold_when_the_masses_wrap():
+    """More than 2^24 samples near the maximum: the sum of the masses wraps at
+    2^64.  2^23 samples at the maximum (mass 2^63), enough at -0.1 to wrap to
+    next to nothing, 2^20 at -8: of the buckets where the wrapped sums reach
+    the target, the first and the third, the highest is taken."""
+    n0, mass = 1 << 23, math.floor(float(np.exp(np.float64(np.float32(-0.1)))) * 2.0 ** 40)
+    n1, n2 = -(-(1 << 63) // mass), 1 << 20
+    n = n0 + n1 + n2
+    _, job = _job(ile.ILE_FP32, seed=96)
+    try:
+        ile.ile_av_reset(job)
+        lw = torch.full((n,), -8.0, dtype=torch.float32, device="cuda")
+        lw[:n0] = 0.0
+        lw[n0:n0 + n1] = -0.1
+        st = ile.ile_av_update(job, 5, 0, 0, n, lw)
+        assert (st.lnL_thr, st.n_min, st.n_live) == (0.0, n0, n)
+    finally:
+        ile.ile_job_release(job)
+
+
 def test_av_threshold_edge_cases(orc):
     """No finite weight keeps the grid; a single finite sample; p_thr = 1 and
     n_min_live above n (every finite sample kept); NaN and +/-0 handled as the
