@@ -278,7 +278,16 @@ extern "C" ile_status ile_fair_draw(ile_job *job, int64_t n, const void *lw, uin
     if (!idx_out && !theta_out) return set_err(ILE_E_INVALID, "no output");
     if (k == 0) return ILE_OK;
     hipStream_t st = (hipStream_t)stream;
-    const size_t need = fair_scratch_bytes(n);
+    // the picks read lw again while they write: outputs that lie over lw get a
+    // copy of it to read, behind the scratch
+    const size_t lw_bytes = (size_t)n * out_size(job->policy), head = align256(fair_scratch_bytes(n));
+    auto over_lw = [&](const void *p, size_t bytes) {
+        const char *a = (const char *)p, *b = (const char *)lw;
+        return p && a < b + lw_bytes && b < a + bytes;
+    };
+    const bool over = over_lw(idx_out, (size_t)k * sizeof(int64_t)) ||
+                      over_lw(theta_out, ((size_t)6 * ld_out + k) * theta_size(job->policy));
+    const size_t need = over ? head + lw_bytes : head;
     if (need > job->fair_cap) {
         hipError_t e = hipStreamSynchronize(st);   // queued draws may still read the old scratch
         if (e != hipSuccess) return dev_fail(job->ctx, e, "sync before fair-draw scratch growth");
@@ -288,8 +297,15 @@ extern "C" ile_status ile_fair_draw(ile_job *job, int64_t n, const void *lw, uin
         if ((s = ctx_alloc(job->ctx, &job->fair_mem, need, "fair-draw scratch")) != ILE_OK) return s;
         job->fair_cap = need;
     }
-    hipError_t e = launch_fair_draw(job->policy, lw, n, seed, round, k, idx_out, theta, ld, theta_out, ld_out,
-                                    job->fair_mem, st);
+    hipError_t e = hipSuccess;
+    if (over) {
+        void *copy = (char *)job->fair_mem + head;
+        e = hipMemcpyAsync(copy, lw, lw_bytes, hipMemcpyDeviceToDevice, st);
+        lw = copy;
+    }
+    if (e == hipSuccess)
+        e = launch_fair_draw(job->policy, lw, n, seed, round, k, idx_out, theta, ld, theta_out, ld_out, job->fair_mem,
+                             st);
     if (e != hipSuccess) return dev_fail(job->ctx, e, "fair draw");
     return ILE_OK;
 }

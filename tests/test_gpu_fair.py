@@ -81,6 +81,33 @@ def test_fair_draw_granules_tiles_runs(orc, n, spread, shift):
     assert np.array_equal(idx.cpu().numpy(), orc.fair_draw(lw, 0xFA2, 5, k))
 
 
+@pytest.mark.parametrize("out", ["idx", "theta"])
+def test_fair_draw_over_its_weights(orc, out):
+    """Outputs that lie over the log-weights: the indices in their place, or a
+    column of the drawn samples.  As from separate buffers."""
+    rng = np.random.default_rng(116)
+    n = 20011
+    lw = rng.normal(0, 2.0, n)
+    th = rng.normal(size=(7, n))
+    job = _job(ile.ILE_FP64, seed=117)
+    ref = orc.fair_draw(lw, 0xFA3, 6, n)
+    try:
+        theta = torch.from_numpy(th).to("cuda")
+        buf = torch.empty((7, n), dtype=torch.float64, device="cuda")
+        buf[4] = torch.from_numpy(lw).to("cuda")
+        if out == "idx":
+            idx = buf[4].view(torch.int64)
+            ile.ile_fair_draw(job, n, buf[4], 0xFA3, 6, n, idx)
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), ref)
+        else:
+            ile.ile_fair_draw(job, n, buf[4], 0xFA3, 6, n, None, theta, n, buf, n)
+            torch.cuda.synchronize()
+            assert np.array_equal(buf.cpu().numpy(), th[:, ref])
+    finally:
+        ile.ile_job_release(job)
+
+
 def test_fair_draw_without_weight_and_errors():
     job = _job(ile.ILE_FP64, seed=112)
     try:
