@@ -138,7 +138,7 @@ def test_av_threshold_when_the_masses_wrap():
         lw[:n0] = 0.0
         lw[n0:n0 + n1] = -0.1
         st = ile.ile_av_update(job, 5, 0, 0, n, lw)
-        assert (st.lnL_thr, st.n_min, st.n_live) == (0.0, n0, n)
+        assert (st["lnL_thr"], st["n_min"], st["n_live"]) == (0.0, n0, n)
     finally:
         ile.ile_job_release(job)
 
