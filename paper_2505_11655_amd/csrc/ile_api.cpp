@@ -109,37 +109,69 @@ bool job_lds_ok(const ile_job *job) {
     return lnl_lds_compiled(job->set, job->kp, job->policy) && job_window_bytes(job, false) <= eval_lds_limit();
 }
 
-// Samples per block of an LDS-staged launch: every block stages its job's
-// window (the time of about kStage samples), one block runs per CU, and a tile
+// Samples per block of an LDS-staged launch, 0 where it is not to be staged.
+// Every block stages its job's window, one block runs per CU, and a tile
 // belongs to one job.  Of 1 to 16 rounds over the 256 CUs, the one whose
-// smallest tile that fits costs least; 0 when that tile is below 512 samples.
-// A sixteenth of a tile stands for the spread of the CUs' speeds, which the
-// last round does not even out: 256 x 2^20 FP32 samples in one round 11.9 ms, in
-// sixteen 10.9.
-static int64_t staged_tile(const std::vector<int64_t> &n) {
-    constexpr int64_t kCus = 256, kStage = 300;
-    int64_t total = 0;
-    for (int64_t v : n) total += v;
-    int64_t best = 0, best_cost = INT64_MAX;
+// smallest tile that fits costs least.  A sixteenth of a tile stands for the
+// spread of the CUs' speeds, which the last round does not even out: 256 x 2^20
+// FP32 samples in one round 11.9 ms, in sixteen 10.9.
+//
+// Staged from 2^17 samples up, two blocks of the unstaged kernel per CU: in
+// FP32 from above that, where a second round of those begins (with 17 modes
+// and more two fill a CU: HLV 17 modes 28 us at 2^17, 38 at 2^17 + 1, staged 33).
+// With the FP32 + FP64 cancellation policy and 17 modes, whose staged kernel
+// has two waves per SIMD, from 896 samples per CU (HLV, 131,073 samples: 46 us
+// staged, 32 unstaged; 230,003: 53, 53; 2^19: 90, 100).  Small jobs share no
+// window: the tiles as they come out, with the time of about 300 samples for
+// the first window and 600 for each that follows it on its CU, have to beat
+// the unstaged kernel, which takes about 1.75 times as long per sample (FP64
+// 2.3, cancellation with 17 modes 1.4).  Unstaged against staged, us, HLV 9
+// modes FP32 / FP64: 1,024 x 300 samples 32, 47 / 58, 70; 512 x 512: 24, 30 / 53,
+// 43; 300 x 700: 24, 33 / 49, 44; 256 x 1,024: 24, 21 / 53, 33; 1,000 x 1,000: 81, 72 /
+// 162, 111.
+static int64_t staged_tile(const std::vector<int64_t> &n, int set, int policy) {
+    constexpr int64_t kCus = 256, kStage = 300, kStageNext = 600;
+    const bool cancel17 = policy == kMixed && set == 2;
+    const int64_t jobs = (int64_t)n.size();
+    int64_t total = 0, longest = 0;
+    for (int64_t v : n) {
+        total += v;
+        longest = std::max(longest, v);
+    }
+    if (total < kCus * (cancel17 ? 896 : 512) + (policy == kFP32 ? 1 : 0)) return 0;
+    auto whole = [](int64_t t) {   // whole waves, and whole blocks of four from 1,024 samples up
+        const int64_t u = t <= 1024 ? 64 : 256;
+        return (t + u - 1) / u * u;
+    };
+    int64_t best = 0, best_cost = INT64_MAX, best_rounds = 0;
     for (int64_t r = 1; r <= 16; r *= 2) {
-        int64_t t = (total / (kCus * r) + 255) / 256 * 256;
-        t = std::max<int64_t>(t, 256);
-        for (;; t = (t + t / 16 + 255) / 256 * 256) {
-            int64_t tiles = 0;
-            for (int64_t v : n) tiles += (v + t - 1) / t;
-            // as many rounds as the jobs alone ask for when they are more than the tiles aimed at
-            const int64_t rounds = (tiles + kCus - 1) / kCus;
-            if (rounds <= r || tiles == (int64_t)n.size()) {
-                const int64_t cost = rounds * (t + kStage) + t / 16;
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best = t;
-                }
-                break;
+        const int64_t slots = kCus * r;
+        int64_t t, tiles = jobs;
+        if (jobs >= slots) {
+            t = whole(longest);   // a tile per job
+        } else if (jobs > slots / 4 * 3 && r < 16) {
+            continue;   // next to a tile per job: the rounds that follow have room
+        } else {
+            for (t = whole((total + slots - 1) / slots); t < longest; t = whole(t + std::max<int64_t>(t / 16, 1))) {
+                const double inv = 1.0 / (double)t, up = (double)t - 0.5;
+                tiles = 0;
+                for (int64_t v : n) tiles += (int64_t)(((double)v + up) * inv);   // ceil(v / t) without the division
+                if (tiles <= slots) break;
+                tiles = jobs;
             }
         }
+        const int64_t rounds = (tiles + kCus - 1) / kCus;
+        const int64_t cost = rounds * (t + kStage) + t / 16;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = t;
+            best_rounds = rounds;
+        }
     }
-    return best >= 512 ? best : 0;
+    const int64_t filled = std::min(best, longest);
+    const double staged = (double)(filled + kStage + (best_rounds - 1) * (filled + kStageNext));
+    const double unstaged = (cancel17 ? 1.4 : policy == kFP64 ? 2.3 : 1.75) * (double)total / kCus;
+    return staged < unstaged ? best : 0;
 }
 
 ile_status ctx_check(ile_ctx *ctx) {
@@ -1019,6 +1051,7 @@ ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStre
         size_t win = 0;
         bool lds_ok = true;
         std::vector<int64_t> ns;
+        ns.reserve(idx.size());
         for (int i : idx) {
             total += items[i].n;
             const ile_job *j = items[i].job;
@@ -1026,14 +1059,11 @@ ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStre
             lds_ok = lds_ok && job_lds_ok(j);
             ns.push_back(items[i].n);
         }
-        // LDS-staged from 512 samples per CU up (2^17 samples, HLV 9 modes, FP64: 30
-        // us against 39 unstaged; 2^20: 114 against 236), in FP32 from above that
-        // (2^17, HL 21 modes: 42 against 38; 2^18, HLV 9 modes: 29 against 44).
-        // Below, and where no window fits: about four 256-thread blocks per CU over
-        // the whole batch (small batches would otherwise leave most CUs idle), 256
-        // to 8192 samples per tile.
-        const int64_t cus = 256, least = cus * 512 + (std::get<2>(g.first) == kFP32 ? 1 : 0);
-        int64_t tile = lds_ok && total >= least ? staged_tile(ns) : 0;
+        // Where not staged: about four 256-thread blocks per CU over the whole batch
+        // (small batches would otherwise leave most CUs idle), 256 to 8192 samples
+        // per tile.
+        const int64_t cus = 256;
+        int64_t tile = lds_ok ? staged_tile(ns, std::get<0>(g.first), std::get<2>(g.first)) : 0;
         const bool lds = tile > 0;
         if (!lds) {
             tile = (total + 4 * cus - 1) / (4 * cus);

@@ -406,6 +406,44 @@ def test_staged_launch_equals_unstaged_slices(policy, modes, sizes):
             ile.ile_job_release(job)
 
 
+@pytest.mark.parametrize("policy", POLICIES, ids=[PNAME[p] for p in POLICIES])
+@pytest.mark.parametrize("modes,sizes", [
+    (5, [131073]), (9, [131073]),                  # the smallest staged FP32 launch (tiles of 576 samples)
+    (5, [90001, 1, 2047, 170003]),                 # ragged tiles of several jobs, every policy staged
+    (17, [229375]), (17, [229376]),                # the smallest staged cancellation launch, and one less
+    (9, [300] * 450 + [77]), (5, [700] * 260),     # jobs too short to stage for
+    (9, [130000] + [100] * 40),                    # whole tiles dealt to the XCDs, short ones after them
+])
+def test_staging_rule_edges(policy, modes, sizes):
+    """Launches on both sides of the staging rule equal launches of at most 30,011
+    samples (never staged) to the bit, job by job."""
+    rng = np.random.default_rng(172 + modes)
+    dt = torch.float64 if policy == ile.ILE_FP64 else torch.float32
+    ot = gu.out_dtype(policy)
+    jobs = [ile.ile_prepare(gu.ctx(), ile.ProblemHost(chirpgen.random_problem(rng, modes, ["H", "L", "V"]),
+                                                      precision=policy)) for _ in range(min(len(sizes), 3))]
+    try:
+        mx = max(sizes)
+        th = torch.from_numpy(np.ascontiguousarray(chirpgen.prior_samples(rng, mx))).to(device="cuda", dtype=dt)
+        use = [jobs[k % len(jobs)] for k in range(len(sizes))]
+        Ls = [torch.empty(n, dtype=ot, device="cuda") for n in sizes]
+        ile.ile_eval_lnL_batch(use, sizes, [th] * len(sizes), [mx] * len(sizes), None, Ls)
+        refs = []
+        for job in jobs:
+            ref = torch.empty(mx, dtype=ot, device="cuda")
+            for a in range(0, mx, 30011):
+                ile.ile_eval_lnL(job, min(30011, mx - a), th.data_ptr() + a * th.element_size(), mx, None,
+                                 ref.data_ptr() + a * ref.element_size())
+            refs.append(ref)
+        torch.cuda.synchronize()
+        for k, (n, L) in enumerate(zip(sizes, Ls)):
+            ref = refs[k % len(jobs)][:n]
+            assert torch.equal(L, ref), (k, n, (L - ref).abs().max())
+    finally:
+        for job in jobs:
+            ile.ile_job_release(job)
+
+
 @pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32])
 def test_marginalize_batch_equals_single(policy):
     """The batched estimator and the single-job one use the same tile for a
