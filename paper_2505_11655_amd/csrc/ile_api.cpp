@@ -927,7 +927,7 @@ static void tmarg_pass(const ile_job *j, int R, int half, int *chunks, int *rows
     *rows = 0;
 }
 
-static void xcd_order(std::vector<Tile> &tiles);
+static void xcd_order(std::vector<Tile> &tiles, int64_t tile);
 
 // Time-marginalised evaluation: jobs grouped by compiled kernel.
 ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R, hipStream_t st) {
@@ -1006,7 +1006,7 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
             for (int64_t t0 = 0; t0 < b.n; t0 += tile) tiles.push_back(Tile{jid, 0, t0, std::min(t0 + tile, b.n)});
         }
         if (tiles.size() > (size_t)INT32_MAX) return set_err(ILE_E_INVALID, "too many samples for one launch");
-        xcd_order(tiles);
+        xcd_order(tiles, tile);
         void *dj = nullptr, *dt = nullptr;
         int slot = -1;
         ile_status s = batch_upload(ctx, ej.data(), ej.size() * sizeof(EvalJob), tiles.data(),
@@ -1021,16 +1021,26 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
 }
 
 // Blocks go to the eight XCDs in turn, each with an L2 of its own: give every
-// XCD a run of consecutive tiles, so that it reads the windows of its own jobs
-// only.
-static void xcd_order(std::vector<Tile> &tiles) {
+// XCD a run of consecutive whole tiles, so that it reads the windows of its own
+// jobs only, and as many as every other.  The jobs' shorter last tiles follow
+// in turn (in the runs, one XCD had whole tiles only and another the short ones:
+// 2^18 and 300 x 3,000 samples, HLV 21 modes, cancellation, 444 us against 364).
+static void xcd_order(std::vector<Tile> &tiles, int64_t tile) {
     constexpr size_t kXcds = 8;
-    const size_t n = tiles.size(), per = n / kXcds, extra = n % kXcds;
-    if (per == 0) return;
+    const size_t n = tiles.size();
+    if (n < kXcds) return;
     std::vector<Tile> out(n);
-    for (size_t h = 0; h < n; h++) {
-        const size_t x = h % kXcds;   // XCD x takes per (+ 1 for the first `extra`) tiles from its start
-        out[h] = tiles[x * per + std::min(x, extra) + h / kXcds];
+    size_t whole = 0;
+    for (const Tile &t : tiles) whole += t.end - t.begin == tile;
+    size_t x = 0, h = 0, rest = whole;
+    for (const Tile &t : tiles) {
+        if (t.end - t.begin != tile) {
+            out[rest++] = t;
+            continue;
+        }
+        out[h] = t;   // XCD x takes the next whole / 8 whole tiles, the first whole mod 8 one more
+        h += kXcds;
+        if (h >= whole) h = ++x;
     }
     tiles.swap(out);
 }
@@ -1084,7 +1094,7 @@ ile_status eval_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, hipStre
             ej.push_back(e);
             for (int64_t t0 = 0; t0 < b.n; t0 += tile) tiles.push_back(Tile{jid, 0, t0, std::min(t0 + tile, b.n)});
         }
-        xcd_order(tiles);
+        xcd_order(tiles, tile);
         void *dj = nullptr, *dt = nullptr;
         int slot = -1;
         ile_status s = batch_upload(ctx, ej.data(), ej.size() * sizeof(EvalJob), tiles.data(),
