@@ -278,24 +278,38 @@ extern "C" ile_status ile_fair_draw(ile_job *job, int64_t n, const void *lw, uin
     if (!idx_out && !theta_out) return set_err(ILE_E_INVALID, "no output");
     if (k == 0) return ILE_OK;
     hipStream_t st = (hipStream_t)stream;
-    // the picks read lw again while they write: outputs that lie over lw get a
-    // copy of it to read, behind the scratch
-    const size_t lw_bytes = (size_t)n * out_size(job->policy), head = align256(fair_scratch_bytes(n));
+    // without a prefix per sample the picks read lw again while they write:
+    // outputs that lie over lw get a copy of it to read, behind the scratch
+    const size_t lw_bytes = (size_t)n * out_size(job->policy);
     auto over_lw = [&](const void *p, size_t bytes) {
         const char *a = (const char *)p, *b = (const char *)lw;
         return p && a < b + lw_bytes && b < a + bytes;
     };
-    const bool over = over_lw(idx_out, (size_t)k * sizeof(int64_t)) ||
-                      over_lw(theta_out, ((size_t)6 * ld_out + k) * theta_size(job->policy));
-    const size_t need = over ? head + lw_bytes : head;
-    if (need > job->fair_cap) {
+    const bool aliased = over_lw(idx_out, (size_t)k * sizeof(int64_t)) ||
+                         over_lw(theta_out, ((size_t)6 * ld_out + k) * theta_size(job->policy));
+    bool all = fair_all(n, k), over = false;
+    size_t head = 0;
+    const std::string prev_err = ile_last_error();   // kept if the smaller scratch serves
+    for (;; all = false) {
+        over = aliased && !all;
+        head = align256(fair_scratch_bytes(n, all));
+        const size_t need = over ? head + lw_bytes : head;
+        if (need <= job->fair_cap) break;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (all && hipStreamIsCapturing(st, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+            continue;   // nothing can grow here: the smaller scratch may be there already
         hipError_t e = hipStreamSynchronize(st);   // queued draws may still read the old scratch
         if (e != hipSuccess) return dev_fail(job->ctx, e, "sync before fair-draw scratch growth");
         ctx_free(job->ctx, job->fair_mem, job->fair_cap);
         job->fair_mem = nullptr;
         job->fair_cap = 0;
-        if ((s = ctx_alloc(job->ctx, &job->fair_mem, need, "fair-draw scratch")) != ILE_OK) return s;
-        job->fair_cap = need;
+        s = ctx_alloc(job->ctx, &job->fair_mem, need, "fair-draw scratch");
+        if (s == ILE_OK) {
+            job->fair_cap = need;
+            set_err(ILE_OK, prev_err);
+            break;
+        }
+        if (!all) return s;
     }
     hipError_t e = hipSuccess;
     if (over) {
@@ -304,8 +318,8 @@ extern "C" ile_status ile_fair_draw(ile_job *job, int64_t n, const void *lw, uin
         lw = copy;
     }
     if (e == hipSuccess)
-        e = launch_fair_draw(job->policy, lw, n, seed, round, k, idx_out, theta, ld, theta_out, ld_out, job->fair_mem,
-                             st);
+        e = launch_fair_draw(job->policy, lw, n, seed, round, k, idx_out, theta, ld, theta_out, ld_out, all,
+                             job->fair_mem, st);
     if (e != hipSuccess) return dev_fail(job->ctx, e, "fair draw");
     return ILE_OK;
 }

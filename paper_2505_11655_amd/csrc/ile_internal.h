@@ -572,13 +572,14 @@ __device__ __forceinline__ unsigned long long mass_fx(double v, double vmax) {
     return (unsigned long long)floor(exp(d) * (double)(1ull << kAvMassBits));
 }
 
-// Fair draws from weighted samples (k_fair.hip): scratch of
-// fair_scratch_bytes(n) bytes; lw in the policy's output type, theta in its
-// theta type.
-size_t fair_scratch_bytes(int64_t n);
+// Fair draws from weighted samples (k_fair.hip): lw in the policy's output type,
+// theta in its theta type.  all: a prefix per sample (which fair_all prefers for
+// many draws) instead of one per 64; scratch of fair_scratch_bytes(n, all) bytes.
+bool fair_all(int64_t n, int64_t k);
+size_t fair_scratch_bytes(int64_t n, bool all);
 hipError_t launch_fair_draw(int policy, const void *lw, int64_t n, uint64_t seed, uint32_t round, int64_t k,
                             int64_t *idx, const void *theta, int64_t ld, void *theta_out, int64_t ld_out,
-                            void *scratch, hipStream_t st);
+                            bool all, void *scratch, hipStream_t st);
 
 // Initial grid: one cell, nb = 1, over the given columns.
 hipError_t launch_av_reset(const AvBufs &b, int d, const int *dims, hipStream_t st);

@@ -81,29 +81,90 @@ def test_fair_draw_granules_tiles_runs(orc, n, spread, shift):
     assert np.array_equal(idx.cpu().numpy(), orc.fair_draw(lw, 0xFA2, 5, k))
 
 
+@pytest.mark.parametrize("n,k", [(20011, 20011), ((1 << 23) + 5, 70001)])
 @pytest.mark.parametrize("out", ["idx", "theta"])
-def test_fair_draw_over_its_weights(orc, out):
+def test_fair_draw_over_its_weights(orc, out, n, k):
     """Outputs that lie over the log-weights: the indices in their place, or a
-    column of the drawn samples.  As from separate buffers."""
+    column of the drawn samples, with a prefix per sample and with one per 64
+    samples (whose picks read the weights again).  As from separate buffers."""
     rng = np.random.default_rng(116)
-    n = 20011
     lw = rng.normal(0, 2.0, n)
-    th = rng.normal(size=(7, n))
     job = _job(ile.ILE_FP64, seed=117)
-    ref = orc.fair_draw(lw, 0xFA3, 6, n)
+    ref = orc.fair_draw(lw, 0xFA3, 6, k)
     try:
-        theta = torch.from_numpy(th).to("cuda")
-        buf = torch.empty((7, n), dtype=torch.float64, device="cuda")
-        buf[4] = torch.from_numpy(lw).to("cuda")
+        buf = torch.zeros(3 * n, dtype=torch.float64, device="cuda")
+        w = buf[n:2 * n]
+        w[:] = torch.from_numpy(lw).to("cuda")
         if out == "idx":
-            idx = buf[4].view(torch.int64)
-            ile.ile_fair_draw(job, n, buf[4], 0xFA3, 6, n, idx)
+            idx = w[n - k:].view(torch.int64)
+            ile.ile_fair_draw(job, n, w, 0xFA3, 6, k, idx)
             torch.cuda.synchronize()
             assert np.array_equal(idx.cpu().numpy(), ref)
         else:
-            ile.ile_fair_draw(job, n, buf[4], 0xFA3, 6, n, None, theta, n, buf, n)
+            th = rng.normal(size=(7, n))
+            theta = torch.from_numpy(th).to("cuda")
+            o = buf[n - k:]   # its second column begins where the weights do
+            if o.numel() < 7 * k:
+                buf = torch.cat([buf, torch.zeros(7 * k, dtype=torch.float64, device="cuda")])
+                w, o = buf[n:2 * n], buf[n - k:]
+            ile.ile_fair_draw(job, n, w, 0xFA3, 6, k, None, theta, n, o, k)
             torch.cuda.synchronize()
-            assert np.array_equal(buf.cpu().numpy(), th[:, ref])
+            assert np.array_equal(o[:7 * k].view(7, k).cpu().numpy(), th[:, ref])
+    finally:
+        ile.ile_job_release(job)
+
+
+@pytest.mark.parametrize("n,k", [((1 << 23), 3001), ((1 << 23) + 1, 3001), ((1 << 23) + 4097, (1 << 17) + 65)])
+def test_fair_draw_prefix_rule(orc, n, k):
+    """Both sides of the rule for the prefixes (per sample up to 2^23 samples and
+    for more than a draw per 64 samples, else per 64 samples): the oracle's
+    indices, and the same where the context's budget holds only the smaller
+    scratch."""
+    rng = np.random.default_rng(118)
+    lw = rng.normal(0, 3.0, n).astype(np.float32)
+    lw[: n // 3] = -np.inf
+    ref = orc.fair_draw(lw.astype(np.float64), 0xFA4, 7, k)
+    lw_d = torch.from_numpy(lw).to("cuda")
+    for budget in (0, 48 << 20):
+        ctx = ile.ile_ctx_create(0, budget)
+        job = ile.ile_prepare(ctx, ile.ProblemHost(chirpgen.random_problem(rng, 5, ["H", "L"]), precision=ile.ILE_FP32))
+        try:
+            idx = torch.full((k,), -7, dtype=torch.int64, device="cuda")
+            ile.ile_fair_draw(job, n, lw_d, 0xFA4, 7, k, idx)
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), ref)
+        finally:
+            ile.ile_job_release(job)
+            ile.ile_ctx_destroy(ctx)
+
+
+def test_fair_draw_capture_after_fewer_draws(orc):
+    """A graph captured after a call with few draws (prefixes by 64 samples) may
+    ask for many: it takes the scratch that is there.  Replays with other
+    work in between equal the oracle."""
+    rng = np.random.default_rng(119)
+    n, k = (1 << 23) + 4097, (1 << 17) + 65
+    lw = rng.normal(0, 3.0, n).astype(np.float32)
+    ref = orc.fair_draw(lw.astype(np.float64), 0xFA5, 8, k)
+    lw_d = torch.from_numpy(lw).to("cuda")
+    job = _job(ile.ILE_FP32, seed=120)
+    try:
+        st = torch.cuda.Stream()
+        idx = torch.full((k,), -7, dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            ile.ile_fair_draw(job, n, lw_d, 0xFA5, 8, 1000, idx, stream=st.cuda_stream)
+        st.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            ile.ile_fair_draw(job, n, lw_d, 0xFA5, 8, k, idx, stream=st.cuda_stream)
+        for _ in range(3):
+            idx.fill_(-7)
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), ref)
+            (lw_d * 2).sum().item()
+        del g
     finally:
         ile.ile_job_release(job)
 
