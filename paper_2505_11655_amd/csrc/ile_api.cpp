@@ -982,11 +982,6 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
             most = 1024;
         }
         const int64_t tile = tmarg_tile(ns, unit, most);
-        if (!rounds) {
-            // as many threads as the tile's iterations share evenly
-            const int64_t iters = (tile + block - 1) / block;
-            block = (int)((tile + iters - 1) / iters + 63) / 64 * 64;
-        }
         std::vector<EvalJob> ej;
         std::vector<Tile> tiles;
         for (int i : idx) {
@@ -1004,6 +999,14 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
             const int jid = (int)ej.size();
             ej.push_back(e);
             for (int64_t t0 = 0; t0 < b.n; t0 += tile) tiles.push_back(Tile{jid, 0, t0, std::min(t0 + tile, b.n)});
+        }
+        if (!rounds) {
+            // As many threads as the tile's iterations share evenly.  A staged tile
+            // of one iteration takes them all, to stage with, while every block
+            // has a CU to itself (HLV 9 modes, R = 4, 64 samples 134 us, 146 with
+            // one wave; 300 x 64 samples 270 us, 168 with one wave).
+            const int64_t iters = (tile + block - 1) / block;
+            if (!staged || iters > 1 || tiles.size() > 256) block = (int)((tile + iters - 1) / iters + 63) / 64 * 64;
         }
         if (tiles.size() > (size_t)INT32_MAX) return set_err(ILE_E_INVALID, "too many samples for one launch");
         xcd_order(tiles, tile);
