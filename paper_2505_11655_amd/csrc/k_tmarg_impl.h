@@ -204,7 +204,10 @@ struct TmargKernel {
                 // recycled one destination register and waited for every
                 // load in turn (37 against 24 ms, 256 x 2^16 samples, HLV 9
                 // modes).  Larger sets, and FP64, go one detector at a time:
-                // holding all their rows costs more registers than it saves.
+                // holding all their rows costs more registers than it saves.  Four
+                // modes at a time, so that the row arrives in the order of its use
+                // (the scheduler turned it round and waited for all of it: 16,384
+                // samples, HL 21 modes, R = 1, 178 us against 147).
                 constexpr int kGroup = (sizeof(TA) == 4 && K * NM <= 27) ? K : 1;
 #pragma unroll
                 for (int k0 = 0; k0 < K; k0 += kGroup) {
@@ -219,6 +222,7 @@ struct TmargKernel {
                             gcpx *qr = (gcpx *)Qg + ((size_t)k * T + ic) * NM;
                             static_for<0, NM>([&](auto A_) {
                                 constexpr int a = decltype(A_)::value;
+                                if constexpr (kGroup == 1 && a > 0 && a % 4 == 0) fence();
                                 qv[kk][a].re = qr[a].re;
                                 qv[kk][a].im = qr[a].im;
                             });
@@ -226,6 +230,7 @@ struct TmargKernel {
                             const cpx<TA> *qr = smem + ((size_t)(k - kGlobalDets) * T + ic) * NM;
                             static_for<0, NM>([&](auto A_) {
                                 constexpr int a = decltype(A_)::value;
+                                if constexpr (kGroup == 1 && a > 0 && a % 4 == 0) fence();
                                 qv[kk][a] = qr[a];
                             });
                         }
@@ -267,6 +272,7 @@ struct TmargKernel {
                     for (int r = 0; r < R; r++) tm = fmax(tm, t1[r]);
                     const TV xm = se * tm;
                     if (xm > mx + kStride && tm > -FLT_MAX) {
+                        asm volatile("");   // a branch: not the exponential and the product at every step
                         sum = (mx > -INFINITY) ? sum * (double)__builtin_amdgcn_exp2f(mx - xm) : 0.0;
                         mx = xm;
                     }
