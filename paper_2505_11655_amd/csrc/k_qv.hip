@@ -614,7 +614,11 @@ struct UvPlan {
     int n_dg, n_sg, n_strip, lcb, n_sl;   // lcb: log2 of the chunk's bins
     int64_t per_sl;                       // bytes of one slice's partials
 };
-UvPlan uv_plan(int64_t n_half, int na, int nd, int np) {
+// Beside the direct sum a block takes two chunks by itself where that is at most
+// twelve bins per lane: the sum's launch costs more (one point and mode, 161
+// bins 97 us a call against 110; 9 modes 111, 117).  The windowed route's calls
+// are shorter and lose by it (9 modes, 252 bins 42 us, 48).
+UvPlan uv_plan(int64_t n_half, int na, int nd, int np, bool win) {
     UvPlan u;
     const int npair = na * (na + 1) / 2;
     u.n_dg = (nd + kUvDet - 1) / kUvDet;
@@ -623,14 +627,16 @@ UvPlan uv_plan(int64_t n_half, int na, int nd, int np) {
     u.lcb = 0;
     while ((2 << u.lcb) <= kUvChunk && ((int64_t)(2 << u.lcb) + 1) * ((int64_t)na * 32 + kUvDet * 16) <= 49152) u.lcb++;
     const int64_t cb = (int64_t)1 << u.lcb, blocks1 = (int64_t)np * u.n_dg * u.n_sg;
-    u.n_sl = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(768 / blocks1, 32), (n_half + cb - 1) / cb));
+    const int64_t chunks = (n_half + cb - 1) / cb, lanes = kQvThreads / std::min(u.n_strip, kQvThreads);
+    const bool one = !win && chunks <= 2 && n_half <= 12 * lanes;
+    u.n_sl = one ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(768 / blocks1, 32), chunks));
     u.per_sl = (int64_t)np * nd * npair * 32;
     return u;
 }
 void launch_uv(const void *hlm, const double *inv_psd, int64_t m_lo, int64_t n_half, int64_t n, int na, int nd, int np,
-               double df, double *part, int64_t part_bytes, void *U, void *V, hipStream_t st) {
+               double df, double *part, int64_t part_bytes, void *U, void *V, bool win, hipStream_t st) {
     const int npair = na * (na + 1) / 2;
-    const UvPlan u = uv_plan(n_half, na, nd, np);
+    const UvPlan u = uv_plan(n_half, na, nd, np, win);
     int64_t n_sl = std::min<int64_t>(u.n_sl, std::max<int64_t>(1, part_bytes / u.per_sl));
     const int64_t uslice = (n_half + n_sl - 1) / n_sl;
     n_sl = (n_half + uslice - 1) / uslice;
@@ -981,7 +987,7 @@ hipError_t launch_qv(const void *hlm, const void *data, const double *inv_psd, i
     hipLaunchKernelGGL(k_qv_reduce, dim3((unsigned)std::min<int64_t>((qe + 255) / 256, 65536)), dim3(256), 0, st,
                        part, ns, cols, n_time, (double2 *)Q);
     launch_uv(hlm, inv_psd, m_lo, n_half, n, na, nd, np, df, (double *)part, (int64_t)ns * cols * n_time * 16, U, V,
-              st);
+              false, st);
     return hipGetLastError();
 }
 
@@ -1103,7 +1109,7 @@ hipError_t launch_qv_dec(const void *hlm, const void *data, const double *inv_ps
     hipLaunchKernelGGL(k_qv_dec_reduce, dim3((unsigned)std::min<int64_t>((qe + 255) / 256, 65536)), dim3(256), 0, st,
                        part, ns, cols, radix, n_t2, n_time, win_half, p_lo, (double2 *)Q);
     launch_uv(hlm, inv_psd, m_lo, n_half, n, na, nd, np, df, (double *)part, (int64_t)ns * cols2 * n_t2 * 16, U, V,
-              st);
+              false, st);
     return hipGetLastError();
 }
 
@@ -1138,7 +1144,7 @@ bool qv_win_ok(int64_t n, int64_t n_band, int n_time) {
 size_t qv_win_scratch_bytes(int64_t n, int64_t n_half, int na, int nd, int np, int n_time) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const WinPlan w = win_plan(n, (int64_t)np * na * nd, n_time);
-    const UvPlan u = uv_plan(n_half, na, nd, np);
+    const UvPlan u = uv_plan(n_half, na, nd, np, true);
     const size_t part = w.n_sl > 1 ? (size_t)w.n_sl * np * nd * na * n_time * 16 : 0;
     return al((size_t)n * 16) + al((size_t)n * nd * w.n_blk * 16) +
            al(std::max<size_t>(part, u.n_sl > 1 ? (size_t)u.n_sl * (size_t)u.per_sl : 0));
@@ -1150,7 +1156,7 @@ hipError_t launch_qv_win(const void *hlm, const void *data, const double *inv_ps
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const int64_t M = n / kWinP, n_pa = (int64_t)np * na, cols = n_pa * nd, m_hi = m_lo + n_half - 1;
     const WinPlan w = win_plan(n, cols, n_time);
-    const UvPlan u = uv_plan(n_half, na, nd, np);
+    const UvPlan u = uv_plan(n_half, na, nd, np, true);
     char *b = (char *)scratch;
     double2 *tw = (double2 *)b;
     b += al((size_t)n * 16);
@@ -1180,7 +1186,8 @@ hipError_t launch_qv_win(const void *hlm, const void *data, const double *inv_ps
         hipLaunchKernelGGL(k_qv_reduce, dim3((unsigned)std::min<int64_t>((qe + 255) / 256, 65536)), dim3(256), 0, st,
                            part, w.n_sl, cols, n_time, (double2 *)Q);
     }
-    launch_uv(hlm, inv_psd, m_lo, n_half, n, na, nd, np, df, (double *)part, (int64_t)u.n_sl * u.per_sl, U, V, st);
+    launch_uv(hlm, inv_psd, m_lo, n_half, n, na, nd, np, df, (double *)part, (int64_t)u.n_sl * u.per_sl, U, V, true,
+              st);
     return hipGetLastError();
 }
 
