@@ -184,7 +184,7 @@ extern "C" ile_status ile_overlaps(ile_ctx *ctx, const ile_qv_shape *sh, const v
     }
     // the automatic route's order: windowed FFT, decimated, direct; a route
     // whose scratch cannot be allocated within the budget gives way to the next
-    bool win = sh->route == ILE_QV_AUTO && qv_win_ok(n, n_band, sh->n_time);
+    bool win = sh->route == ILE_QV_AUTO && qv_win_ok(n, n_band, cols, sh->n_time);
     auto plan = [&](bool w, int r, int &ns_, size_t &need_) {
         ns_ = w ? 1 : r ? qv_dec_slices(n, cols, sh->n_time, sh->win_half, r) : qv_slices(n_band, cols, sh->n_time);
         need_ = w   ? qv_win_scratch_bytes(n, n_half, sh->n_modes, sh->n_det, sh->n_points, sh->n_time)

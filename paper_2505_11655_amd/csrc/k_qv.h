@@ -17,9 +17,9 @@ namespace ile {
 int qv_radix(int64_t n, int64_t n_band, int n_time, int win_half, bool force);
 
 // Whether the windowed-FFT route applies (n a multiple of its 512-point
-// transforms) and its estimated cost is below the direct sum's; its scratch;
-// Q by this route, U and V.
-bool qv_win_ok(int64_t n, int64_t n_band, int n_time);
+// transforms, its launches within a grid) and its estimated cost is below the
+// direct sum's; its scratch; Q by this route, U and V.
+bool qv_win_ok(int64_t n, int64_t n_band, int64_t cols, int n_time);
 size_t qv_win_scratch_bytes(int64_t n, int64_t n_half, int na, int nd, int np, int n_time);
 hipError_t launch_qv_win(const void *hlm, const void *data, const double *inv_psd, int64_t n, int na, int nd, int np,
                          double df, int64_t m_lo, int64_t n_half, int n_time, int win_half, void *Q, void *U, void *V,

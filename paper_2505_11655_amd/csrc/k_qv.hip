@@ -1134,10 +1134,13 @@ WinPlan win_plan(int64_t n, int64_t cols, int n_time) {
 
 }  // namespace
 
-bool qv_win_ok(int64_t n, int64_t n_band, int n_time) {
+bool qv_win_ok(int64_t n, int64_t n_band, int64_t cols, int n_time) {
     if (n % kWinP != 0 || n >= ((int64_t)1 << 31)) return false;
-    const int64_t n_blk = (n_time + kWinP - 1) / kWinP;
-    return (double)kWinCost * (double)(n * n_blk) <
+    const WinPlan w = win_plan(n, cols, n_time);
+    // a launch's grid holds it: the blocks of k_qv_win in x, the window blocks of
+    // k_qv_wprep in z
+    if (cols * w.n_blk * w.n_sl > INT32_MAX || w.n_blk > 65535) return false;
+    return (double)kWinCost * (double)(n * w.n_blk) <
            (double)((n_time + kQvTT - 1) / kQvTT * kQvTT + 49) * (double)n_band;
 }
 
@@ -1173,8 +1176,7 @@ hipError_t launch_qv_win(const void *hlm, const void *data, const double *inv_ps
     const unsigned pb = (unsigned)std::min<int64_t>((n + kQvThreads - 1) / kQvThreads, 4096);
     hipLaunchKernelGGL(k_qv_wprep, dim3(pb, (unsigned)nd, (unsigned)w.n_blk), dim3(kQvThreads), 0, st,
                        (const double2 *)data, inv_psd, n, nd, df, m_lo, m_hi, win_half, tw, D);
-    const int64_t blocks = cols * w.n_blk * w.n_sl;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const int64_t blocks = cols * w.n_blk * w.n_sl;   // qv_win_ok: a grid holds them
     const size_t lds = (size_t)kWinC * kWinX * 8 + 64 * 16 + (size_t)__builtin_popcount(slabs) * kWinSlab * 16;
     hipError_t e = hipFuncSetAttribute((const void *)k_qv_win, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
