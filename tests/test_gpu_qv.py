@@ -290,6 +290,45 @@ def test_overlaps_auto_falls_back_to_direct_within_budget(orc):
         _close(Vg[p], Vo)
 
 
+@pytest.mark.parametrize("n,npt,na,nd,n_time,win_half,f_hi,budget,falls_to", [
+    (16384, 1, 1, 8, 1024, 512, 0.25, 6, "decimated"),    # windowed: 5.3 MiB (a class of 8); decimated: 3.3 (4)
+    (16384, 1, 1, 3, 16384, 8192, 0.05, 16, "direct"),    # windowed: 30 MiB (32); no radix for the window; direct: 3.4
+    (16400, 96, 9, 3, 410, 205, 0.25, 768, "direct"),     # no windowed route; decimated: 700 MiB (1 GiB); direct: 480
+])
+def test_overlaps_routes_give_way_within_budget(orc, n, npt, na, nd, n_time, win_half, f_hi, budget, falls_to):
+    """The automatic route in contexts whose budget (MiB) holds the scratch of the
+    route it falls to and not of the one before: the Q of that route to the bit,
+    which the unlimited context does not take, and no error left behind."""
+    rng = np.random.default_rng(143 + n + nd)
+    hl = rng.normal(size=(npt, na, n)) + 1j * rng.normal(size=(npt, na, n))
+    data = rng.normal(size=(nd, n)) + 1j * rng.normal(size=(nd, n))
+    df = 1.0 / n
+    route = ile.ILE_QV_DECIMATED if falls_to == "decimated" else ile.ILE_QV_DIRECT
+    forced = _gpu(hl, data, df, 0.001, f_hi, n_time, win_half, route=route)
+    free = _gpu(hl, data, df, 0.001, f_hi, n_time, win_half, route=ile.ILE_QV_AUTO)
+    assert not np.array_equal(free[0], forced[0])
+    ctx = ile.ile_ctx_create(0, budget * 2 ** 20)
+    try:
+        h, d = torch.from_numpy(hl).to("cuda"), torch.from_numpy(data).to("cuda")
+        Q = torch.zeros((npt, nd, na, n_time), dtype=torch.complex128, device="cuda")
+        U = torch.zeros((npt, nd, na, na), dtype=torch.complex128, device="cuda")
+        V = torch.zeros_like(U)
+        with pytest.raises(Exception, match="bad overlap route"):
+            ile.ile_overlaps(ctx, h, d, df, 0.001, f_hi, n_time, win_half, Q, U, V, route=7)
+        ile.ile_overlaps(ctx, h, d, df, 0.001, f_hi, n_time, win_half, Q, U, V)
+        assert ile.lib().ile_last_error() == b"bad overlap route"
+        torch.cuda.synchronize()
+    finally:
+        ile.ile_ctx_destroy(ctx)
+    Qg, Ug, Vg = Q.cpu().numpy(), U.cpu().numpy(), V.cpu().numpy()
+    assert np.array_equal(Qg, forced[0])
+    for p in sorted({0, npt - 1}):
+        Qo, Uo, Vo = orc.overlaps_qv(hl[p], data, None, df, 0.001, f_hi, n_time, win_half)
+        _close(Qg[p], Qo)
+        _close(Ug[p], Uo)
+        _close(Vg[p], Vo)
+
+
 def test_overlaps_full_size_sampled(orc):
     """The benchmark's launch shape: 256 points x 9 modes x 3 detectors on
     the 16384-bin grid (20-1024 Hz, the centred 410-sample window), seeded
