@@ -1123,7 +1123,17 @@ ile_status batch_upload(ile_ctx *ctx, const void *a, size_t na, const void *b, s
     hipError_t e;
     if (!sl.ev && (e = hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming)) != hipSuccess)
         return dev_fail(ctx, e, "event create");
-    if (sl.armed && (e = hipEventSynchronize(sl.ev)) != hipSuccess) return dev_fail(ctx, e, "scratch slot wait");
+    if (sl.armed && (e = hipEventSynchronize(sl.ev)) != hipSuccess) {
+        // The stream of the slot's last launch may be gone (a caller may destroy a
+        // stream once its work is done), and the event with it.  The slot is free
+        // when the device is idle; if that cannot be had, the error is real.
+        (void)hipGetLastError();
+        if (hipDeviceSynchronize() != hipSuccess) return dev_fail(ctx, e, "scratch slot wait");
+        (void)hipEventDestroy(sl.ev);
+        sl.ev = nullptr;
+        if ((e = hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming)) != hipSuccess)
+            return dev_fail(ctx, e, "event create");
+    }
     sl.armed = false;
     if (need > sl.cap) {
         if (sl.d) (void)hipFree(sl.d);

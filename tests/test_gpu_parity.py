@@ -444,6 +444,33 @@ def test_staging_rule_edges(policy, modes, sizes):
             ile.ile_job_release(job)
 
 
+def test_streams_of_the_caller_may_go():
+    """Streams that a caller makes, uses, synchronises and destroys, one after the
+    other and more of them than the context has scratch slots, leave nothing that
+    later calls on other streams wait for in vain."""
+    import ctypes as C
+
+    hip = C.CDLL(ile.LIB_PATH)   # the HIP runtime the library is linked to
+    rng = np.random.default_rng(173)
+    job = ile.ile_prepare(gu.ctx(), ile.ProblemHost(chirpgen.random_problem(rng, 5, ["H", "L"]), precision=ile.ILE_FP64))
+    try:
+        n = 1000
+        th = torch.from_numpy(np.ascontiguousarray(chirpgen.prior_samples(rng, n))).to("cuda")
+        ref, _ = gu.gpu_eval(job, th.cpu().numpy(), ile.ILE_FP64)
+        for _ in range(20):
+            st = C.c_void_p()
+            assert hip.hipStreamCreateWithFlags(C.byref(st), 1) == 0
+            L = torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+            torch.cuda.synchronize()
+            ile.ile_eval_lnL(job, n, th, n, None, L, stream=st.value)
+            assert hip.hipStreamSynchronize(st) == 0 and hip.hipStreamDestroy(st) == 0
+            assert np.array_equal(L.cpu().numpy(), ref)
+        for _ in range(10):
+            assert np.array_equal(gu.gpu_eval(job, th.cpu().numpy(), ile.ILE_FP64)[0], ref)
+    finally:
+        ile.ile_job_release(job)
+
+
 @pytest.mark.parametrize("policy", [ile.ILE_FP64, ile.ILE_FP32])
 def test_marginalize_batch_equals_single(policy):
     """The batched estimator and the single-job one use the same tile for a
