@@ -517,6 +517,8 @@ typedef struct {
     int64_t t_arrival_ns, t_admit_ns, t_start_ns, t_finish_ns;  /* steady clock */
 } ile_result;
 
+/* After a wait or poll that returns ILE_OK for a job whose status is an error,
+ * ile_last_error() gives the message of the call that failed for it. */
 ile_status ile_server_create(ile_ctx *ctx, const ile_server_opts *opts, ile_server **out);
 ile_status ile_server_submit(ile_server *srv, const ile_problem *problem, const ile_job_opts *opts,
                              uint64_t *job_id);

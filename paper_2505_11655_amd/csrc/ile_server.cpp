@@ -31,6 +31,7 @@
 #include <deque>
 #include <memory>
 #include <mutex>
+#include <string>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -75,6 +76,7 @@ struct Req {
     ReqState state = kQueued;
     bool cancel = false;
     ile_result res{};
+    std::string err;          // why it failed (the failing call's message)
 };
 
 }  // namespace
@@ -104,6 +106,7 @@ struct ile_server {
     hipEvent_t up_ev = nullptr;
     bool up_pending = false;   // uploads queued on `up` since the last wait (scheduler thread only)
     bool failed = false;
+    std::string fail_msg;      // of the call that ended the pass
 };
 
 namespace {
@@ -157,6 +160,7 @@ size_t footprint_of(const ile_server *s, const Req *r) {
 
 void finish(ile_server *s, Req *r, int status, const ile_marg *m) {
     r->res.status = status;
+    if (status != ILE_OK && status != ILE_E_CANCELLED) r->err = s->failed ? s->fail_msg : ile_last_error();
     if (m) r->res.marg = *m;
     r->res.rounds = r->rounds;
     r->res.samples = r->done;
@@ -277,8 +281,12 @@ void pre_admit(ile_server *s) {
 bool run_pass(ile_server *s, std::vector<Req *> &act) {
     hipStream_t st = s->stream;
     if (s->up_pending) {   // the inputs of the jobs admitted since the last pass
-        if (hipEventRecord(s->up_ev, s->up) != hipSuccess || hipStreamWaitEvent(st, s->up_ev, 0) != hipSuccess)
+        hipError_t e = hipEventRecord(s->up_ev, s->up);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, s->up_ev, 0);
+        if (e != hipSuccess) {
+            (void)dev_fail(nullptr, e, "server pass: uploads");
             return false;
+        }
         s->up_pending = false;
     }
     const int64_t t_start = now_ns();
@@ -302,9 +310,13 @@ bool run_pass(ile_server *s, std::vector<Req *> &act) {
             th_out = (char *)r->d_pth + (size_t)r->rounds * r->chunk * theta_bytes(policy);
             ld = r->pool_cap;
             lnl_out = (char *)r->d_pL + (size_t)r->rounds * r->chunk * lnl_bytes(policy);
-            if (r->rounds >= 1 && hipMemcpyAsync(r->d_hist + r->rounds, r->job->d_gmm, sizeof(GmmDev),
-                                                 hipMemcpyDeviceToDevice, st) != hipSuccess)
+            const hipError_t e = r->rounds >= 1 ? hipMemcpyAsync(r->d_hist + r->rounds, r->job->d_gmm, sizeof(GmmDev),
+                                                                 hipMemcpyDeviceToDevice, st)
+                                                : hipSuccess;
+            if (e != hipSuccess) {
+                (void)dev_fail(nullptr, e, "server pass: proposal history");
                 return false;
+            }
         }
         const BatchItem bi{r->job, n, th_out, ld, r->d_lr, lnl_out, r->d_lw};
         (r->jo.tmarg_oversample == 4 ? tm4 : r->jo.tmarg_oversample == 1 ? tm1 : items).push_back(bi);
@@ -551,11 +563,13 @@ void scheduler(ile_server *s) {
         s->cv_done.notify_all();
         if (act.empty()) continue;
         if (!run_pass(s, act)) {
+            const std::string why = ile_last_error();   // before the calls below
             // nothing queued may still use freed buffers
             if (s->up) (void)hipStreamSynchronize(s->up);
             (void)hipStreamSynchronize(s->stream);
             std::lock_guard<std::mutex> lk(s->mu);
             s->failed = true;
+            s->fail_msg = why;
             for (Req *r : s->active) finish(s, r, ILE_E_DEVICE, nullptr);
             s->active.clear();
             for (Req *r : s->ready) finish(s, r, ILE_E_DEVICE, nullptr);
@@ -647,7 +661,7 @@ extern "C" ile_status ile_server_submit(ile_server *s, const ile_problem *Pin, c
     r->res.t_arrival_ns = now_ns();
     r->res.status = ILE_PENDING;
     std::lock_guard<std::mutex> lk(s->mu);
-    if (s->failed) return set_err(ILE_E_DEVICE, "server failed after a device error");
+    if (s->failed) return set_err(ILE_E_DEVICE, "server failed after a device error: " + s->fail_msg);
     r->id = s->next_id++;
     *job_id = r->id;
     s->queue.push_back(r.get());
@@ -662,7 +676,9 @@ extern "C" ile_status ile_server_poll(ile_server *s, uint64_t id, ile_result *ou
     auto it = s->all.find(id);
     if (it == s->all.end()) return set_err(ILE_E_INVALID, "unknown job id");
     *out = it->second->res;
-    return it->second->state == kDone ? ILE_OK : ILE_PENDING;
+    if (it->second->state != kDone) return ILE_PENDING;
+    if (!it->second->err.empty()) set_err(ILE_OK, it->second->err);
+    return ILE_OK;
 }
 
 extern "C" ile_status ile_server_wait(ile_server *s, uint64_t id, int64_t timeout_ms, ile_result *out) {
@@ -679,6 +695,7 @@ extern "C" ile_status ile_server_wait(ile_server *s, uint64_t id, int64_t timeou
         return set_err(ILE_E_TIMEOUT, "wait timed out");
     }
     *out = r->res;
+    if (!r->err.empty()) set_err(ILE_OK, r->err);
     return ILE_OK;
 }
 

@@ -444,3 +444,25 @@ def test_pooled_sheared_mixture_job_matches_oracle_loop(orc, pool):
     assert alone.rounds == len(ths)
     assert abs(alone.marg.ln_L - o["ln_L"]) <= 1e-8 * max(1.0, abs(o["ln_L"]))
     assert abs(alone.marg.n_eff - o["n_eff"]) <= 1e-6 * o["n_eff"]
+
+
+def test_failed_job_keeps_the_message(pool):
+    """A job whose admission fails ends with the failing call's status, and wait
+    and poll leave that call's message, made on the server's own thread, as the
+    last error of the thread that asks; the server goes on."""
+    ctx = ile.ile_ctx_create(0, 12 << 20)          # holds the small job's buffers, not the large one's
+    srv = ile.ile_server_create(ctx, max_active=4, hbm_budget_bytes=1 << 30, chunk_samples=1 << 20)
+    try:
+        big, _k1 = _submit(srv, (pool[0], ile.ILE_FP32, False, 1 << 20, 1, 0))
+        r = ile.ile_server_wait(srv, big, 60000)
+        assert r.status == -3                       # ILE_E_TOO_BIG
+        assert b"device budget exceeded allocating" in ile.lib().ile_last_error()
+        with pytest.raises(Exception, match="unknown job id"):
+            ile.ile_server_poll(srv, 10 ** 6)
+        ile.ile_server_poll(srv, big)
+        assert b"device budget exceeded allocating" in ile.lib().ile_last_error()
+        small, _k2 = _submit(srv, (pool[0], ile.ILE_FP32, False, 1 << 12, 2, 0))
+        assert ile.ile_server_wait(srv, small, 60000).status == 0
+    finally:
+        ile.ile_server_destroy(srv)
+        ile.ile_ctx_destroy(ctx)
