@@ -514,13 +514,6 @@ __global__ void __launch_bounds__(kEmThreads) k_em_init(const EmJob *__restrict_
     block_sum<kMom>(acc, J.work + Lo.init + blockIdx.x, Lo.nblk);
 }
 
-// Component index of moment 8 + lane (second moments, row by row), lane < 28.
-__device__ __forceinline__ void mom_ab(int t, int &a, int &b) {
-    a = 0;
-    while ((a + 1) * (a + 2) / 2 <= t) a++;
-    b = t - a * (a + 1) / 2;
-}
-
 // One wave per component: covariance rows from the moments s[36] (LDS),
 // centred on the mean offsets, plus the floor; the lane's row (lane < d).
 __device__ __forceinline__ void wave_cov(const double *s, const PriorDev &pr, const GmmDev &g, int lane, int d,

@@ -60,13 +60,6 @@ struct TmargKernel {
     static constexpr bool kExp2 = sizeof(TV) == 4;
     static constexpr float kStride = 8.0f;
 
-    __device__ __forceinline__ static TA expT(TA x) {
-        if constexpr (sizeof(TA) == 4)
-            return __expf(x);
-        else
-            return exp(x);
-    }
-
     __device__ __forceinline__ static void run(const EvalJob &J, const int64_t begin, const int64_t end,
                                                cpx<TA> *smem) {
         const int T = J.n_time;
@@ -177,7 +170,7 @@ struct TmargKernel {
             if constexpr (kExp2) {
                 se = (TV)((double)s * 1.4426950408889634074);
                 if (!(se > (TV)0)) in_lo = INT32_MAX;   // D infinite: every step as one at an edge
-                // (lanes past the last sample read as 0, which can only narrow the range)
+                // (whatever lanes past the last sample give can only narrow the range)
 #pragma unroll
                 for (int m = 1; m < 64; m <<= 1) {
                     in_lo = max(in_lo, __shfl_xor(in_lo, m));
@@ -286,7 +279,7 @@ struct TmargKernel {
                         for (int r = 0; r < R; r++) part += __builtin_amdgcn_exp2f(fma(se, t1[r], -mx));
                     }
                     sum += (double)part;
-                } else {
+                } else {   // (node values in FP64)
                     TV x[R];
                     TV cmax = (TV)-INFINITY;
 #pragma unroll
@@ -304,21 +297,13 @@ struct TmargKernel {
                         cmax = fmax(cmax, x[r]);
                     }
                     if (cmax > mx) {
-                        if constexpr (DM)
-                            sum = (mx > -INFINITY) ? sum * exp(mx - cmax) : 0.0;
-                        else
-                            sum = (mx > (TA)-INFINITY) ? sum * (double)expT(mx - cmax) : 0.0;
+                        sum = (mx > -INFINITY) ? sum * exp(mx - cmax) : 0.0;
                         mx = cmax;
                     }
-                    TV part = (TV)0;
+                    double part = 0.0;
 #pragma unroll
-                    for (int r = 0; r < R; r++) {
-                        if constexpr (DM)
-                            part += (x[r] > -INFINITY) ? exp(x[r] - mx) : 0.0;
-                        else
-                            part += (x[r] > (TA)-INFINITY) ? expT(x[r] - mx) : (TA)0;
-                    }
-                    sum += (double)part;
+                    for (int r = 0; r < R; r++) part += (x[r] > -INFINITY) ? exp(x[r] - mx) : 0.0;
+                    sum += part;
                 }
             }
             if constexpr (!kT2First) {
