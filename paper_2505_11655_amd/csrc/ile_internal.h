@@ -463,7 +463,7 @@ struct AvDev {
     int32_t nb_next;      // of the grid the last update built
     int32_t cur;          // which cell buffer holds the current grid
     int32_t valid;        // the last update found a finite sample
-    uint32_t done;        // blocks of the running kernel that are through
+    int32_t pad_;
     int64_t n_cells, n_cells_next;
     double ln_vol;        // ln V = ln n_cells - d ln nb
     // last update

@@ -149,7 +149,6 @@ __global__ void __launch_bounds__(kAvThreads) k_av_begin(const AvJob *__restrict
                 S.last_cnt[c] = 0;
             }
             S.valid = 0;
-            S.done = 0;
             S.thr = -INFINITY;
             S.n_min = 0;
             S.n_live = J.n;
@@ -162,27 +161,6 @@ __global__ void __launch_bounds__(kAvThreads) k_av_begin(const AvJob *__restrict
         J.b.hkey[i] = kEmpty;
         J.b.hidx[i] = kNoSlot;
     }
-}
-
-// True in every thread of the last of a job's `blocks` blocks to get here; what
-// the others wrote before is then visible to agent-scope loads.  Every thread
-// releases before the barrier: the barrier alone does not wait for the other
-// waves' global atomics and stores, and thread 0's fence covers its own wave's.
-__device__ __forceinline__ bool av_last(AvDev &S, unsigned blocks) {
-    __shared__ bool last;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        last = atomicAdd(&S.done, 1u) == blocks - 1;
-        if (last) S.done = 0;   // for the next kernel
-    }
-    __syncthreads();
-    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return last;
-}
-template <class T>
-__device__ __forceinline__ T av_fresh(const T *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <class TO>
@@ -223,16 +201,14 @@ __global__ void __launch_bounds__(kAvThreads) k_av_max(const AvJob *__restrict__
     }
 }
 
-template <class TO>
-__device__ void av_pick(const AvJob &J, int shift);
-
 // One radix-select pass: digit (key >> shift) & 255 of every finite sample
 // whose higher digits match the chain's prefix; chain 0 counts and sums the
-// fixed-point masses, chain 1 counts.  The job's last block picks the digits.
-// Bound by latency: the samples' LDS atomics on few buckets and the chain of
-// four (FP64 eight) passes, so four samples per thread and no launch of its own
-// for the pick (2^16 FP32 samples: 9 us a pass, 18 with sixteen per thread and a
-// pick kernel that scanned through LDS).
+// fixed-point masses, chain 1 counts.  Bound by latency: the samples' LDS atomics
+// on few buckets and the chain of four (FP64 eight) passes, so few samples per
+// thread.  The digits are a launch of their own: a last block that picks them
+// needs every wave of every block to write its L2 back before it reports
+// (2^16 samples, an update and two draws: FP32 98 us against 91, FP64 137, 122;
+// 2^20: 244, 202 and 325, 245).
 template <class TO>
 __global__ void __launch_bounds__(kAvThreads) k_av_hist(const AvJob *__restrict__ jobs, int shift) {
     AV_JOB;
@@ -262,8 +238,6 @@ __global__ void __launch_bounds__(kAvThreads) k_av_hist(const AvJob *__restrict_
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * 256 * 2; i += kAvThreads)
         if (h[i]) atomicAdd(&J.b.hist[i], h[i]);
-    const int64_t blocks = (J.n + kAvThreads - 1) / kAvThreads;
-    if (av_last(S, (unsigned)(blocks < gridDim.x ? blocks : gridDim.x))) av_pick<TO>(J, shift);
 }
 
 // Inclusive sums over the block's 256 threads of a and b.
@@ -295,17 +269,19 @@ __device__ __forceinline__ void block_scan2(unsigned long long &a, unsigned long
 // the chosen digit is the highest bucket where the chain's target is reached.
 // After the last pass: the threshold, n_min and eq. (nbins_V).
 template <class TO>
-__device__ void av_pick(const AvJob &J, int shift) {
+__global__ void __launch_bounds__(kAvThreads) k_av_pick(const AvJob *__restrict__ jobs, int shift) {
+    AV_JOB;
     constexpr int nbits = sizeof(TO) * 8;
     AvDev &S = *J.b.st;
+    if (S.n_fin == 0) return;
     unsigned long long *H = J.b.hist;
     const int t = threadIdx.x, d = 255 - t;
     __shared__ unsigned long long sh_prefix[2], sh_count[2], sh_total;
     unsigned long long cc[2], mm[2], suf_c[2], suf_m[2];
 #pragma unroll
     for (int c = 0; c < 2; c++) {
-        cc[c] = av_fresh(&H[(c * 256 + d) * 2 + 0]);
-        mm[c] = av_fresh(&H[(c * 256 + d) * 2 + 1]);
+        cc[c] = H[(c * 256 + d) * 2 + 0];
+        mm[c] = H[(c * 256 + d) * 2 + 1];
     }
 #pragma unroll
     for (int c = 0; c < 2; c++) {
@@ -435,13 +411,10 @@ __device__ __forceinline__ int64_t av_span(int64_t n) {
     return (n + (int64_t)kAvThreads * 4096 - 1) / ((int64_t)kAvThreads * 4096) * kAvThreads;
 }
 
-// First samples of every span, a wave at a span; the job's last block turns the
-// counts into offsets (in place), which gives the new number of cells, and makes
-// the new grid the current one.  (The last block's turn costs every block a
-// fence: 2^16 samples in 256 blocks 12 us, in 64 8.)
+// First samples of every span, a wave at a span.
 __global__ void __launch_bounds__(kAvThreads) k_av_count(const AvJob *__restrict__ jobs) {
     AV_JOB;
-    AvDev &S = *J.b.st;
+    const AvDev &S = *J.b.st;
     constexpr int kWaves = kAvThreads / 64;
     const int64_t span = av_span(J.n);
     const int nblk = (int)((J.n + span - 1) / span);
@@ -456,15 +429,23 @@ __global__ void __launch_bounds__(kAvThreads) k_av_count(const AvJob *__restrict
         }
         if ((threadIdx.x & 63) == 0) J.b.bcnt[sp] = (uint32_t)cnt;
     }
-    const unsigned blocks = (unsigned)((nblk + kWaves - 1) / kWaves);
-    if (!av_last(S, blocks < gridDim.x ? blocks : gridDim.x)) return;
+}
+
+// The spans' counts into offsets (in place), which gives the new number of
+// cells, and the new grid made the current one.
+__global__ void __launch_bounds__(kAvThreads) k_av_scan(const AvJob *__restrict__ jobs) {
+    AV_JOB;
+    AvDev &S = *J.b.st;
+    if (!S.valid) return;
+    const int64_t span = av_span(J.n);
+    const int nblk = (int)((J.n + span - 1) / span);
     const int per = (nblk + kAvThreads - 1) / kAvThreads;   // at most 16
     const int lo = threadIdx.x * per;
     uint32_t c[16];
     unsigned long long sum = 0, none = 0;
 #pragma unroll
     for (int i = 0; i < 16; i++) {
-        c[i] = i < per && lo + i < nblk ? av_fresh(&J.b.bcnt[lo + i]) : 0u;
+        c[i] = i < per && lo + i < nblk ? J.b.bcnt[lo + i] : 0u;
         sum += c[i];
     }
     unsigned long long run = sum;
@@ -523,12 +504,13 @@ __global__ void __launch_bounds__(kAvThreads) k_av_compact(const AvJob *__restri
 // Blocks per job: samples per thread from `least` (few samples, every kernel is
 // a chain of latency: 2^16 samples draw in 4.7 us and insert in 6.8 with one per
 // thread, 9.2 and 15 with four) to `most`, which a launch reaches as it fills
-// the chip (the blocks' merges, fences and shared state then cost more than the
-// chains: 100 jobs served, 2^16 samples a round, 106 ms with up to sixteen,
-// 129 with the least).
-int grid_for(int64_t n, int n_jobs, int least, int most) {
-    const int64_t fill = n * n_jobs / ((int64_t)kAvThreads * 512);
-    const int64_t per = std::max<int64_t>(least, std::min<int64_t>(most, fill));
+// the chip, with `fill` blocks (the blocks' merges and shared state then cost
+// more than the chains: 100 jobs served, 2^16 samples a round, 106 ms with up to
+// sixteen, 129 with the least; the maximum of 2^20 samples 11.5 us in 256 blocks,
+// 16 in 512).
+int grid_for(int64_t n, int n_jobs, int least, int most, int fill) {
+    const int64_t want = n * n_jobs / ((int64_t)kAvThreads * fill);
+    const int64_t per = std::max<int64_t>(least, std::min<int64_t>(most, want));
     const int64_t g = (n + kAvThreads * per - 1) / (kAvThreads * per);
     return (int)(g < 1 ? 1 : (g > 4096 ? 4096 : g));
 }
@@ -537,16 +519,21 @@ template <class TO>
 hipError_t av_update_t(const AvJob *d, int n_jobs, int64_t nmax, hipStream_t st) {
     constexpr int nbits = sizeof(TO) * 8;
     const unsigned nz = (unsigned)n_jobs;
+    const dim3 threads(kAvThreads), one(1, 1, nz);
     uint64_t used = 1024;
     while (used < (uint64_t)2 * (uint64_t)nmax) used <<= 1;
-    hipLaunchKernelGGL(k_av_begin, dim3(grid_for((int64_t)used, n_jobs, 4, 4), 1, nz), dim3(kAvThreads), 0, st, d);
-    hipLaunchKernelGGL(k_av_max<TO>, dim3(grid_for(nmax, n_jobs, 4, 16), 1, nz), dim3(kAvThreads), 0, st, d);
-    for (int shift = nbits - 8; shift >= 0; shift -= 8)
-        hipLaunchKernelGGL(k_av_hist<TO>, dim3(grid_for(nmax, n_jobs, 4, 16), 1, nz), dim3(kAvThreads), 0, st, d, shift);
-    hipLaunchKernelGGL(k_av_insert<TO>, dim3(grid_for(nmax, n_jobs, 1, 4), 1, nz), dim3(kAvThreads), 0, st, d);
+    hipLaunchKernelGGL(k_av_begin, dim3(grid_for((int64_t)used, n_jobs, 4, 4, 512), 1, nz), threads, 0, st, d);
+    const dim3 g(grid_for(nmax, n_jobs, 4, 16, 256), 1, nz);
+    hipLaunchKernelGGL(k_av_max<TO>, g, threads, 0, st, d);
+    for (int shift = nbits - 8; shift >= 0; shift -= 8) {
+        hipLaunchKernelGGL(k_av_hist<TO>, g, threads, 0, st, d, shift);
+        hipLaunchKernelGGL(k_av_pick<TO>, one, threads, 0, st, d, shift);
+    }
+    hipLaunchKernelGGL(k_av_insert<TO>, dim3(grid_for(nmax, n_jobs, 1, 4, 512), 1, nz), threads, 0, st, d);
     const int nblk = (int)std::min<int64_t>((nmax + kAvThreads - 1) / kAvThreads, 4096);
-    hipLaunchKernelGGL(k_av_count, dim3(std::min(grid_for(nmax, n_jobs, 4, 16), (nblk + 3) / 4), 1, nz), dim3(kAvThreads), 0, st, d);
-    hipLaunchKernelGGL(k_av_compact, dim3(nblk, 1, nz), dim3(kAvThreads), 0, st, d);
+    hipLaunchKernelGGL(k_av_count, dim3((nblk + 3) / 4, 1, nz), threads, 0, st, d);
+    hipLaunchKernelGGL(k_av_scan, one, threads, 0, st, d);
+    hipLaunchKernelGGL(k_av_compact, dim3(nblk, 1, nz), threads, 0, st, d);
     return hipGetLastError();
 }
 
@@ -568,7 +555,7 @@ hipError_t launch_av_reset(const AvBufs &b, int d, const int *dims, hipStream_t 
 hipError_t launch_av_draw(int policy, const AvJob *d_jobs, const AvJob *h_jobs, int n_jobs, hipStream_t st) {
     const int64_t nmax = max_n(h_jobs, n_jobs);
     if (n_jobs <= 0 || nmax <= 0) return hipSuccess;
-    const dim3 grid(grid_for(nmax, n_jobs, 1, 4), 1, (unsigned)n_jobs);
+    const dim3 grid(grid_for(nmax, n_jobs, 1, 4, 512), 1, (unsigned)n_jobs);
     if (policy == kFP64)
         hipLaunchKernelGGL(k_av_draw<double>, grid, dim3(kAvThreads), 0, st, d_jobs);
     else

@@ -1,7 +1,8 @@
-"""The hand-over to a job's last block (adaptive volume), read from the compiled
-kernels: every wave has to wait for its own global stores and atomics before the
-barrier that precedes the block's arrival, since neither the barrier nor
-another wave's fence waits for them."""
+"""What one step of an adaptive-volume update hands to the next goes through a
+launch of its own, read from the compiled kernels.  A counter by which a job's
+last block takes over from the others is sound only if every wave waits for its
+global stores and atomics at agent scope before the block reports, since neither
+a barrier nor another wave's fence does; there is none."""
 import os
 import re
 import subprocess
@@ -9,8 +10,6 @@ import subprocess
 import pytest
 
 from paper_2505_11655_amd import build
-
-KERNELS = ["k_av_histIfE", "k_av_histIdE", "k_av_countE"]
 
 
 @pytest.fixture(scope="module")
@@ -21,22 +20,10 @@ def listing(tmp_path_factory):
     return open(out).read()
 
 
-@pytest.mark.parametrize("name", KERNELS)
-def test_every_wave_drains_before_the_arrival(listing, name):
+@pytest.mark.parametrize("name", ["k_av_histIf", "k_av_histId", "k_av_count"])
+def test_no_block_waits_for_the_others(listing, name):
     m = re.search(r"^(\w*" + name + r"\w*):.*?^\s*\.end_amdhsa_kernel", listing, re.S | re.M)
     assert m, "kernel not found"
-    code = [t for t in (l.split(";")[0].strip() for l in m.group(0).splitlines()) if t and not t.startswith(".")]
-    # the arrival: the only 32-bit add whose old value comes back
-    arrive = [i for i, t in enumerate(code) if re.match(r"(global|flat)_atomic_add v\d+, .*sc0", t)]
-    assert len(arrive) == 1, arrive
-    barrier = max(i for i in range(arrive[0]) if code[i].startswith("s_barrier"))
-    drained = released = False
-    for t in reversed(code[:barrier]):
-        if t.startswith("s_waitcnt") and "vmcnt(0)" in t:
-            drained = True
-        if drained and t.startswith("buffer_wbl2"):
-            released = True
-            break
-        assert not re.match(r"(global|flat|buffer)_(store|atomic)", t), f"in flight at the barrier: {t}"
-        assert not t.startswith("s_barrier"), "no release between the barriers"
-    assert drained and released
+    code = [l.split(";")[0].strip() for l in m.group(0).splitlines()]
+    # an arrival: a 32-bit add whose old value comes back
+    assert not [t for t in code if re.match(r"(global|flat)_atomic_(add|inc) v\d+, .*sc0", t)]
