@@ -16,11 +16,13 @@
 //      formed again.  With total = 0 the index is -1.
 // What bounds it: the two reads of lw.  By granules only 0.125 B per sample is
 // written, where a prefix per sample costs 8 B, but a draw costs up to 64
-// exponentials one after the other.  So by samples up to 2^23 samples, where the
-// call is latency, and above with more than a draw per 64 samples.  By samples
-// against by granules, FP32, us per call: n = 100, k = 1,000 12, 28; 65,537, 1,000
-// 19, 32; 2^20, 2^20 74, 181; 2^22, 2^10 36, 41; 2^24, 2^16 90, 82; 2^24, 2^18 112, 116;
-// 2^26, 2^16 341, 231; 2^26, 2^20 528, 504; 2^26, 2^22 1190, 1233.
+// exponentials one after the other.  So by samples where the call is latency, up
+// to 1.5 x 2^20 samples, and above with more than a draw per 16 samples.  By
+// samples against by granules, FP32, us per call: weights of an event, to 4,096
+// draws, 2^12 samples 16, 17; 2^16 15, 23; 2^20 17, 24; 2^21 18, 18; FP64, 2^22 29, 22;
+// 2^18 draws 33, 28.  Weights spread so that every sample has mass: 100 samples to
+// 1,000 draws 12, 28; 2^20 to 2^20 74, 181; 2^22 to 2^18 51, 75, to 2^20 109, 210; 2^26
+// to 2^20 528, 504, to 2^22 1190, 1233.
 // Measured, FP32, 2^26 samples to 2^20 draws: max 49 us (5.5 TB/s; 173 us with
 // one load in flight per lane and an atomic per wave), sums 47 us (597 us for
 // tile sums plus a prefix per sample in two passes), pick 43 us (32 us from a
@@ -41,8 +43,8 @@ constexpr int kFairTileGran = kFairTile / kFairGran;       // 64: one granule pe
 constexpr int kFairRuns = 2048;                            // most runs (blocks of k_fair_sums): 8 per CU
 constexpr int kFairMaxBlocks = 1024;                       // most blocks of k_fair_max: 4 per CU
 constexpr uint32_t kFairAttempt = 5;
-constexpr int64_t kFairAllSamples = 1 << 23;               // a prefix per sample up to so many samples,
-constexpr int64_t kFairAllDraws = 64;                      // or with more than a draw per so many
+constexpr int64_t kFairAllSamples = 3 << 19;               // a prefix per sample up to so many samples,
+constexpr int64_t kFairAllDraws = 16;                      // or with more than a draw per so many
 static_assert(kFairTileGran == 64, "the granules of a tile are scanned by one wave");
 
 // Scratch: [0] max key, [1 .. 1 + kFairMaxBlocks) the blocks' max keys,

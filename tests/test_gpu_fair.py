@@ -114,10 +114,10 @@ def test_fair_draw_over_its_weights(orc, out, n, k):
         ile.ile_job_release(job)
 
 
-@pytest.mark.parametrize("n,k", [((1 << 23), 3001), ((1 << 23) + 1, 3001), ((1 << 23) + 4097, (1 << 17) + 65)])
+@pytest.mark.parametrize("n,k", [((3 << 19), 3001), ((3 << 19) + 1, 3001), ((1 << 23) + 4097, (1 << 19) + 257)])
 def test_fair_draw_prefix_rule(orc, n, k):
-    """Both sides of the rule for the prefixes (per sample up to 2^23 samples and
-    for more than a draw per 64 samples, else per 64 samples): the oracle's
+    """Both sides of the rule for the prefixes (per sample up to 1.5 x 2^20 samples and
+    for more than a draw per 16 samples, else per 64 samples): the oracle's
     indices, and the same where the context's budget holds only the smaller
     scratch."""
     rng = np.random.default_rng(118)
@@ -125,7 +125,7 @@ def test_fair_draw_prefix_rule(orc, n, k):
     lw[: n // 3] = -np.inf
     ref = orc.fair_draw(lw.astype(np.float64), 0xFA4, 7, k)
     lw_d = torch.from_numpy(lw).to("cuda")
-    for budget in (0, 48 << 20):
+    for budget in (0, 48 << 20 if n > 1 << 23 else 8 << 20):
         ctx = ile.ile_ctx_create(0, budget)
         job = ile.ile_prepare(ctx, ile.ProblemHost(chirpgen.random_problem(rng, 5, ["H", "L"]), precision=ile.ILE_FP32))
         try:
@@ -143,7 +143,7 @@ def test_fair_draw_capture_after_fewer_draws(orc):
     ask for many: it takes the scratch that is there.  Replays with other
     work in between equal the oracle."""
     rng = np.random.default_rng(119)
-    n, k = (1 << 23) + 4097, (1 << 17) + 65
+    n, k = (1 << 23) + 4097, (1 << 19) + 257
     lw = rng.normal(0, 3.0, n).astype(np.float32)
     ref = orc.fair_draw(lw.astype(np.float64), 0xFA5, 8, k)
     lw_d = torch.from_numpy(lw).to("cuda")
