@@ -139,7 +139,10 @@ static int64_t staged_tile(const std::vector<int64_t> &n, int set, int policy) {
         longest = std::max(longest, v);
     }
     if (total < kCus * (cancel17 ? 896 : 512) + (policy == kFP32 ? 1 : 0)) return 0;
-    auto whole = [](int64_t t) {   // whole waves, and whole blocks of four from 1,024 samples up
+    // sized in whole waves up to 1,024 samples, launched in whole blocks of four
+    // (5 x 27,032 samples, FP64, 17 modes: tiles of 576 are as long as tiles of 768
+    // and more, 194 us a step against 182)
+    auto whole = [](int64_t t) {
         const int64_t u = t <= 1024 ? 64 : 256;
         return (t + u - 1) / u * u;
     };
@@ -171,7 +174,7 @@ static int64_t staged_tile(const std::vector<int64_t> &n, int set, int policy) {
     const int64_t filled = std::min(best, longest);
     const double staged = (double)(filled + kStage + (best_rounds - 1) * (filled + kStageNext));
     const double unstaged = (cancel17 ? 1.4 : policy == kFP64 ? 2.3 : 1.75) * (double)total / kCus;
-    return staged < unstaged ? best : 0;
+    return staged < unstaged ? (best + 255) / 256 * 256 : 0;
 }
 
 ile_status ctx_check(ile_ctx *ctx) {
@@ -1024,10 +1027,13 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
 }
 
 // Blocks go to the eight XCDs in turn, each with an L2 of its own: give every
-// XCD a run of consecutive whole tiles, so that it reads the windows of its own
-// jobs only, and as many as every other.  The jobs' shorter last tiles follow
-// in turn (in the runs, one XCD had whole tiles only and another the short ones:
-// 2^18 and 300 x 3,000 samples, HLV 21 modes, cancellation, 444 us against 364).
+// XCD a run of consecutive tiles, so that it reads the windows of its own jobs
+// only.  Where more than one tile in sixteen is a job's shorter last one, the runs
+// are of whole tiles, as many for every XCD, and the short ones follow in turn
+// (in the runs, one XCD had whole tiles only and another the short ones: 2^18 and
+// 300 x 3,000 samples, HLV 21 modes, cancellation, 444 us against 341).  Fewer stay
+// in the runs: a block away from its job's others reads its window alone (5 x
+// 27,032 samples, FP64, 17 modes: 187 us a step against 180).
 static void xcd_order(std::vector<Tile> &tiles, int64_t tile) {
     constexpr size_t kXcds = 8;
     const size_t n = tiles.size();
@@ -1035,13 +1041,15 @@ static void xcd_order(std::vector<Tile> &tiles, int64_t tile) {
     std::vector<Tile> out(n);
     size_t whole = 0;
     for (const Tile &t : tiles) whole += t.end - t.begin == tile;
+    const bool all = (n - whole) * 16 <= n;
+    if (all) whole = n;
     size_t x = 0, h = 0, rest = whole;
     for (const Tile &t : tiles) {
-        if (t.end - t.begin != tile) {
+        if (!all && t.end - t.begin != tile) {
             out[rest++] = t;
             continue;
         }
-        out[h] = t;   // XCD x takes the next whole / 8 whole tiles, the first whole mod 8 one more
+        out[h] = t;   // XCD x takes the next whole / 8 tiles, the first whole mod 8 one more
         h += kXcds;
         if (h >= whole) h = ++x;
     }
