@@ -116,9 +116,11 @@ bool job_lds_ok(const ile_job *job) {
 // spread of the CUs' speeds, which the last round does not even out: 256 x 2^20
 // FP32 samples in one round 11.9 ms, in sixteen 10.9.
 //
-// Staged from 2^17 samples up, two blocks of the unstaged kernel per CU: in
-// FP32 from above that, where a second round of those begins (with 17 modes
-// and more two fill a CU: HLV 17 modes 28 us at 2^17, 38 at 2^17 + 1, staged 33).
+// Staged from 2^17 samples up, two blocks of the unstaged kernel per CU.  In
+// FP32 from above that with 17 modes and more, where two blocks fill a CU and a
+// second round of them begins (HLV 17 modes 28 us at 2^17, 38 at 2^17 + 1, staged
+// 33), and from 576 samples per CU with fewer (HLV 9 modes, 2^17 + 1: 20 us a call,
+// staged 23; 150,001: 23, 22).
 // With the FP32 + FP64 cancellation policy and 17 modes, whose staged kernel
 // has two waves per SIMD, from 896 samples per CU (HLV, 131,073 samples: 46 us
 // staged, 32 unstaged; 230,003: 53, 53; 2^19: 90, 100).  Small jobs share no
@@ -138,7 +140,8 @@ static int64_t staged_tile(const std::vector<int64_t> &n, int set, int policy) {
         total += v;
         longest = std::max(longest, v);
     }
-    if (total < kCus * (cancel17 ? 896 : 512) + (policy == kFP32 ? 1 : 0)) return 0;
+    const bool fp32 = policy == kFP32;
+    if (total < kCus * (cancel17 ? 896 : fp32 && set <= 1 ? 576 : 512) + (fp32 && set >= 2 ? 1 : 0)) return 0;
     // sized in whole waves up to 1,024 samples, launched in whole blocks of four
     // (5 x 27,032 samples, FP64, 17 modes: tiles of 576 are as long as tiles of 768
     // and more, 194 us a step against 182)
@@ -1027,13 +1030,11 @@ ile_status tmarg_batch(ile_ctx *ctx, const std::vector<BatchItem> &items, int R,
 }
 
 // Blocks go to the eight XCDs in turn, each with an L2 of its own: give every
-// XCD a run of consecutive tiles, so that it reads the windows of its own jobs
-// only.  Where more than one tile in sixteen is a job's shorter last one, the runs
-// are of whole tiles, as many for every XCD, and the short ones follow in turn
-// (in the runs, one XCD had whole tiles only and another the short ones: 2^18 and
-// 300 x 3,000 samples, HLV 21 modes, cancellation, 444 us against 341).  Fewer stay
-// in the runs: a block away from its job's others reads its window alone (5 x
-// 27,032 samples, FP64, 17 modes: 187 us a step against 180).
+// XCD a run of consecutive whole tiles, so that it reads the windows of its own
+// jobs only, and as many as every other.  The jobs' shorter last tiles follow
+// in turn (in the runs, one XCD had whole tiles only and another the short ones:
+// 2^18 and 300 x 3,000 samples, HLV 21 modes, cancellation, 444 us against 341;
+// and a last round of one tile should be a short one).
 static void xcd_order(std::vector<Tile> &tiles, int64_t tile) {
     constexpr size_t kXcds = 8;
     const size_t n = tiles.size();
@@ -1041,11 +1042,9 @@ static void xcd_order(std::vector<Tile> &tiles, int64_t tile) {
     std::vector<Tile> out(n);
     size_t whole = 0;
     for (const Tile &t : tiles) whole += t.end - t.begin == tile;
-    const bool all = (n - whole) * 16 <= n;
-    if (all) whole = n;
     size_t x = 0, h = 0, rest = whole;
     for (const Tile &t : tiles) {
-        if (!all && t.end - t.begin != tile) {
+        if (t.end - t.begin != tile) {
             out[rest++] = t;
             continue;
         }

@@ -408,7 +408,7 @@ def test_staged_launch_equals_unstaged_slices(policy, modes, sizes):
 
 @pytest.mark.parametrize("policy", POLICIES, ids=[PNAME[p] for p in POLICIES])
 @pytest.mark.parametrize("modes,sizes", [
-    (5, [131073]), (9, [131073]),                  # the smallest staged FP32 launch (tiles of 768 samples)
+    (5, [147456]), (9, [147455]), (17, [131073]),  # the smallest staged FP32 launches, and one sample less
     (5, [90001, 1, 2047, 170003]),                 # ragged tiles of several jobs, every policy staged
     (17, [229375]), (17, [229376]),                # the smallest staged cancellation launch, and one less
     (9, [300] * 450 + [77]), (5, [700] * 260),     # jobs too short to stage for
