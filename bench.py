@@ -42,7 +42,7 @@ LNL_BYTES = {"fp32": 40, "fp64": 80}
 # the kernel executes (64 lanes x (add + mul + 2 fma + trans) per wave
 # instruction): 2,437 FP32 + 108 FP64 (sky direction and delays).
 LNL_TRAFFIC = {"fetch_B_per_sample": 32.093, "write_B_per_sample": 8.000, "executed_flop_per_sample": 2545.0,
-               "src_sha256": "c9bd33a91dfeea330965929b2b792277e7c7a74ab059b71f08d0bd6450880fa8"}
+               "src_sha256": "5a5f54748a279b42390ee710c024821f0a8547f87d65d1c9ddd0c67de9260f23"}
 # algorithmic HBM bytes per sample of the draw (7 theta + ln p - ln p_s
 # written) and estimator (lw read) kernels
 DRAW_BYTES = {"fp32": 32, "fp64": 64}
@@ -425,7 +425,8 @@ def overlaps_leg(ile, torch, ctx, stream, n_points=256, n_modes=9, n_det=3, reps
     flop_uv = 2 * 8.0 * (n_modes * (n_modes + 1) // 2) * n_band * n_points * n_det
     out = {"points": n_points, "modes": n_modes, "detectors": n_det, "band_bins": n_band, "window": 410}
     Qs = {}
-    for name, route in (("direct", ile.ILE_QV_DIRECT), ("decimated", ile.ILE_QV_DECIMATED)):
+    for name, route in (("direct", ile.ILE_QV_DIRECT), ("decimated", ile.ILE_QV_DECIMATED),
+                        ("automatic", ile.ILE_QV_AUTO)):
         ile.ile_overlaps(ctx, hlm, data, df, 20.0, 1024.0, 410, 205, Q, U, V, stream=stream, route=route)
         t0 = time.perf_counter()
         for _ in range(reps):
@@ -448,10 +449,12 @@ def overlaps_leg(ile, torch, ctx, stream, n_points=256, n_modes=9, n_det=3, reps
                      "direct_equivalent_TFLOPs": (flop_direct + flop_uv) / (gms * 1e-3) / 1e12}
     dq = (Qs["direct"] - Qs["decimated"]).abs().max().item() / Qs["direct"].abs().max().item()
     out["decimated_vs_direct_max_rel_diff"] = dq
+    out["automatic_vs_direct_max_rel_diff"] = ((Qs["direct"] - Qs["automatic"]).abs().max().item()
+                                               / Qs["direct"].abs().max().item())
     out["speedup_gpu"] = out["direct"]["ms_per_call_gpu"] / out["decimated"]["ms_per_call_gpu"]
     out["note"] = ("direct: 410 x 8034 bins per column on the FP64 matrix cores; decimated: radix-16 partial "
-                   "sums, then 32 x 1024 bins per column (26 decimated times used); flop figures count the "
-                   "direct sum's work")
+                   "sums, then 32 x 1024 bins per column (26 decimated times used); automatic: interleaved "
+                   "512-point transforms over the window; flop figures count the direct sum's work")
     del hlm, data, Q, U, V, Qs, busy_a
     torch.cuda.empty_cache()
     return out

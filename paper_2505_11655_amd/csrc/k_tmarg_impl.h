@@ -55,8 +55,8 @@ struct TmargKernel {
     // of kStride (a new origin costs an exponential and an FP64 product, and
     // every lane rises to its maximum through many), which keeps an exponent's
     // rounding below 2^-21.  Masks only at the steps where a lane of the wave
-    // has a node outside.  Bound by the vector unit (203 instructions per
-    // step); 16 x 16,384 samples, HLV 9 modes, R = 4: 391 to 365 us.
+    // has a node outside.  Bound by the vector unit (189 instructions per
+    // step); 16 x 16,384 samples, HLV 9 modes, R = 4: 391 to 364 us.
     static constexpr bool kExp2 = sizeof(TV) == 4;
     static constexpr float kStride = 8.0f;
 
